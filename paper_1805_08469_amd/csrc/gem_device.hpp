@@ -61,12 +61,10 @@ __host__ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, ui
 // general IEEE sequences' range handling has nothing to do.  hipcc lowers a / b
 // to scale operands near the ends of the exponent range, refine a hardware
 // reciprocal by Newton steps with fma residual corrections, and fix up special
-// values; sqrt(x) to scale tiny x, take the hardware root and step to the
-// neighbour whose fma residual has the right sign, then handle 0 and inf.  On
-// operands with no scaling and no special value the core steps alone give the
-// same, correctly rounded, result -- which the self-test library checks
-// exhaustively over the domains used below and on a wide random sample for
-// the guarded quotient.
+// values; sqrt(x) likewise scales and fixes up.  On operands with no scaling
+// and no special value fewer steps give the same, correctly rounded, result --
+// which the self-test library checks exhaustively over the domains used below
+// and on a wide random sample for the guarded quotient.
 // ---------------------------------------------------------------------------
 
 // a / b, correctly rounded, for normal b and a quotient well inside the
@@ -83,17 +81,21 @@ __device__ __forceinline__ float div_rn_core(float a, float b)
     return __builtin_fmaf(e3, r, q);
 }
 
-// sqrt(x), correctly rounded, for x = +0 or normal x (no scaling).
-__device__ __forceinline__ float sqrt_rn_core(float x)
+// sqrt(x), correctly rounded, for the Box-Muller radicands x = -2 ln(k 2^-24),
+// k in [1, 2^24] (+0 or in [1.1e-7, 33.3]).  One Newton step from the hardware
+// reciprocal root y: g = x y, then g + (x - g^2) (y / 2).  The step is the
+// correctly rounded root for every one of the 2^24 radicands (the self-test
+// library checks all of them on the device).  Five instructions and the root;
+// stepping v_sqrt's result to the neighbour with the right residual sign takes
+// eight.  x = 0 takes y = 2^50, so g = 0 and the correction is 0; y / 2 is an
+// integer step of the exponent.
+__device__ __forceinline__ float radicand_root(float x)
 {
-    const float y = __builtin_amdgcn_sqrtf(x);
-    const float dn = __uint_as_float(__float_as_uint(y) - 1u);
-    const float up = __uint_as_float(__float_as_uint(y) + 1u);
-    const float r_dn = __builtin_fmaf(-dn, y, x);
-    const float r_up = __builtin_fmaf(-up, y, x);
-    float r = (r_dn <= 0.0f) ? dn : y;
-    r = (r_up > 0.0f) ? up : r;
-    return r;
+    const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(x, 0x1p-100f));
+    const float g = x * y;
+    const float half_y = __uint_as_float(__float_as_uint(y) - 0x00800000u);
+    const float e = __builtin_fmaf(-g, g, x);
+    return __builtin_fmaf(e, half_y, g);
 }
 
 // num / den, correctly rounded for every input: the core steps when both
@@ -110,8 +112,9 @@ __device__ __forceinline__ float div_rn(float num, float den)
 }
 
 // (f - 1) / (f + 1), correctly rounded, for the binary32 f in (sqrt(1/2),
-// sqrt(2)] the logarithm below reduces to: the hardware reciprocal r of
-// f + 1 and one residual correction of the quotient (f - 1) r.  f - 1 is exact,
+// sqrt(2)] the logarithm below reduces to (or that times a power of two): the
+// hardware reciprocal r of f + 1 and one residual correction of the quotient
+// (f - 1) r.  f - 1 is exact,
 // f + 1 lies in (1.7, 2.5), and on these 2^23 operand pairs the two steps
 // give the correctly rounded quotient every time (the self-test library
 // checks all of them on the device against the IEEE division); the general
@@ -125,58 +128,59 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 }
 
 // ---------------------------------------------------------------------------
-// Natural logarithm of u = k * 2^-24 for an integer k in [1, 2^24] (the Box-
-// Muller radius argument).  u = 2^e f with f in (sqrt(1/2), sqrt(2)];
-// ln f = 2 atanh((f-1)/(f+1)) by its series to the s^9 term (Abramowitz &
-// Stegun 4.1.27); ln u = e ln2 + ln f with ln 2 split into a 15-bit head and
-// a binary32 tail so that e * head is exact.
+// The Box-Muller radicand -2 ln u of u = k * 2^-24, k in [1, 2^24].
+// u = 2^e f with f in (sqrt(1/2), sqrt(2)]; ln f = 2 atanh((f-1)/(f+1)) by its
+// series to the s^9 term (Abramowitz & Stegun 4.1.27); ln u = e ln2 + ln f
+// with ln 2 split into a 15-bit head and a binary32 tail so that e * head is
+// exact.
+//
+// The defined steps are p = ((s^2/9 + 1/7) s^2 + 1/5) s^2 + 1/3, p s^2, then
+// ln f = fma(2s, p s^2, 2s), ln u = fma(e, head, fma(e, tail, ln f)) and the
+// radicand -2 ln u.  Here every value carries the power-of-two factor that
+// makes the doublings and the final -2 disappear: s' = -4 s (the quotient of
+// -4 (f - 1), exact), s'^2 = 16 s^2 against coefficients divided by 16 per
+// degree, and the tail and head times -2.  Scaling by a power of two commutes
+// with rounding (nothing here is subnormal or overflows), so the bits are
+// those of the defined steps, in 2 instructions fewer.
+//
+// The reduction works on the integer: k as binary32 (exact) has u's
+// significand and an exponent 24 larger; subtracting the bits of 2^24 * the
+// least binary32 above sqrt(1/2) leaves e in the bits above the significand
+// and f's significand offset below them.
 // ---------------------------------------------------------------------------
-
-// ln of the positive normal binary32 value with bit pattern `bits`, scaled by
-// 2^(127 - bias): bias 127 gives ln of the value itself.
-__device__ __forceinline__ float ln_from_bits(uint32_t bits, int bias)
+__device__ __forceinline__ float radicand_of_k24(uint32_t k)
 {
-    int e = static_cast<int>(bits >> 23) - bias;  // positive: the sign bit is clear
-    const uint32_t mant = bits & 0x007FFFFFu;
-    const bool upper = mant > 0x003504F3u;        // 1.mant above sqrt(2) in binary32
-    const uint32_t fbits = mant | (upper ? 0x3F000000u : 0x3F800000u);
-    e += upper ? 1 : 0;
-    const float f = __uint_as_float(fbits);
-    const float s = ln_quotient(f - 1.0f, f + 1.0f);
+    constexpr uint32_t kLeast = 0x3F3504F4u;   // least binary32 above sqrt(1/2)
+    const uint32_t ix = __float_as_uint(static_cast<float>(k)) - (kLeast + (24u << 23));
+    const float ef = static_cast<float>(static_cast<int32_t>(ix) >> 23);
+    const float f = __uint_as_float((ix & 0x007FFFFFu) + kLeast);
+    const float s = ln_quotient(__builtin_fmaf(f, -4.0f, 4.0f), f + 1.0f);   // -4 (f-1)/(f+1)
     const float z = s * s;
-    float p = 1.0f / 9.0f;
-    p = __builtin_fmaf(p, z, 1.0f / 7.0f);
-    p = __builtin_fmaf(p, z, 1.0f / 5.0f);
-    p = __builtin_fmaf(p, z, 1.0f / 3.0f);
+    float p = (1.0f / 9.0f) * 0x1p-16f;
+    p = __builtin_fmaf(p, z, (1.0f / 7.0f) * 0x1p-12f);
+    p = __builtin_fmaf(p, z, (1.0f / 5.0f) * 0x1p-8f);
+    p = __builtin_fmaf(p, z, (1.0f / 3.0f) * 0x1p-4f);
     p = p * z;
-    const float two_s = s + s;
-    const float ln_f = __builtin_fmaf(two_s, p, two_s);
-    const float ef = static_cast<float>(e);
-    const float ln2_tail = 0x1.7f7d1cp-20f;   // RN(ln 2 - ln2_head)
+    const float ln_f = __builtin_fmaf(s, p, s);   // -2 ln f
+    const float ln2_tail = 0x1.7f7d1cp-20f;       // RN(ln 2 - ln2_head)
     const float ln2_head = 0x1.62e4p-1f;
-    float r = __builtin_fmaf(ef, ln2_tail, ln_f);
-    r = __builtin_fmaf(ef, ln2_head, r);
-    return r;
+    const float r = __builtin_fmaf(ef, -2.0f * ln2_tail, ln_f);
+    return __builtin_fmaf(ef, -2.0f * ln2_head, r);
 }
 
-// ln u for u = k 2^-24 in (0, 1].
-__device__ __forceinline__ float ln_of_unit(float u) { return ln_from_bits(__float_as_uint(u), 127); }
-
-// The same from k: the binary32 k (exact) has the significand of u and an
-// exponent 24 larger, so the scaling by 2^-24 folds into the exponent's bias
-// instead of a multiplication.
-__device__ __forceinline__ float ln_of_k24(uint32_t k)
+// r cos(phi) and r sin(phi) for phi = 2 pi (xb >> 8) / 2^24.  With k = xb >> 8,
+// the angle is reduced to the nearest quarter turn on the integer, exactly;
+// the rest, |x| <= pi/4, goes through the Taylor series of sin (to x^9) and
+// cos (to x^10).  k minus its nearest multiple of 2^22 is k's low 22 bits
+// read as a signed number.
+//
+// Quadrant q (bits 30 and 31 of xb + 2^29): (sin, cos) = (sx, cx), (cx, -sx),
+// (-sx, -cx), (-cx, sx): an odd quadrant takes (cx, -sx), and quadrants 2 and
+// 3 negate both, which here goes into r's sign before the two products (a
+// product's bits but for its sign do not depend on its factors' signs).
+__device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, float& zs)
 {
-    return ln_from_bits(__float_as_uint(static_cast<float>(k)), 127 + 24);
-}
-
-// sin and cos of 2 pi k / 2^24, k in [0, 2^24).  The angle is reduced to the
-// nearest quarter turn on the integer, exactly; the rest, |x| <= pi/4, goes
-// through the Taylor series of sin (to x^9) and cos (to x^10).
-__device__ __forceinline__ void sincos_of_turn(uint32_t k, float& sn, float& cs)
-{
-    const uint32_t quarter = (k + 0x00200000u) >> 22;
-    const int rem = static_cast<int>(k) - static_cast<int>(quarter << 22);
+    const int rem = static_cast<int>(xb << 2) >> 10;
     const float step = 6.28318530717958647692f * 0x1p-24f;   // RN(2 pi) 2^-24
     const float x = static_cast<float>(rem) * step;
     const float x2 = x * x;
@@ -195,32 +199,19 @@ __device__ __forceinline__ void sincos_of_turn(uint32_t k, float& sn, float& cs)
     pc = __builtin_fmaf(pc, x2, -0.5f);
     const float cx = __builtin_fmaf(pc, x2, 1.0f);
 
-    // Quadrant q = quarter mod 4 (bits 22 and 23 of k + 2^21): sin takes sx, cx,
-    // -sx, -cx and cos cx, -sx, -cx, sx.  On the bits: an odd quadrant swaps
-    // the two (a bit-select under a mask of bit 22), quadrants 2 and 3 negate
-    // sin (bit 23 into the sign) and quadrants 1 and 2 negate cos (bit 22 xor
-    // bit 23) -- negation flips the sign bit, as -x does.
-    const uint32_t kq = k + 0x00200000u;
-    const uint32_t odd = static_cast<uint32_t>(static_cast<int32_t>(kq << 9) >> 31);
-    const uint32_t sxb = __float_as_uint(sx), cxb = __float_as_uint(cx);
-    const uint32_t a = (odd & cxb) | (~odd & sxb);     // |sin| candidate
-    const uint32_t b = (odd & sxb) | (~odd & cxb);     // |cos| candidate
-    const uint32_t neg_s = (kq << 8) & 0x80000000u;
-    const uint32_t neg_c = ((kq << 8) ^ (kq << 9)) & 0x80000000u;
-    sn = __uint_as_float(a ^ neg_s);
-    cs = __uint_as_float(b ^ neg_c);
+    const bool odd = static_cast<int32_t>((xb << 1) + 0x40000000u) < 0;   // bit 30 of xb + 2^29
+    // r ^ ((xb + 2^29) & sign bit): one V_BITOP3_B32 (a ^ (b & c), table 0x78)
+    const float rs = __uint_as_float(__builtin_amdgcn_bitop3_b32(
+        __float_as_uint(r), xb + 0x20000000u, 0x80000000u, 0x78));
+    zs = rs * (odd ? cx : sx);
+    zc = rs * (odd ? -sx : cx);
 }
 
 // Box-Muller (1958): from two words, u1 = ((xa >> 8) + 1) 2^-24 in (0, 1] and
 // the angle index xb >> 8, the pair r cos(phi), r sin(phi), r = sqrt(-2 ln u1).
 __device__ __forceinline__ void box_muller(uint32_t xa, uint32_t xb, float& zc, float& zs)
 {
-    // -2 ln u1 is +0 (u1 = 1) or at least 1.1e-7: no scaling.
-    const float r = sqrt_rn_core(-2.0f * ln_of_k24((xa >> 8) + 1u));
-    float sn, cs;
-    sincos_of_turn(xb >> 8, sn, cs);
-    zc = r * cs;
-    zs = r * sn;
+    turn_times(radicand_root(radicand_of_k24((xa >> 8) + 1u)), xb, zc, zs);
 }
 
 // Four standard normals for elements 4q..4q+3 at clock t.

@@ -90,9 +90,11 @@ __device__ __forceinline__ int scale_bin(float x)
 // diagnostics): the same arithmetic as commit_element, with one range check
 // for the four quotients.  When all eight operand magnitudes lie in
 // [2^-60, 2^60], each quotient is div_rn_core -- what div_rn takes for each of
-// them; otherwise each goes through div_rn.  fmaxf / fminf skip a NaN
-// operand, which may then reach div_rn_core: its quotient is NaN there as in
-// the general division, and the clamp makes either pi = 0.
+// them; otherwise each goes through div_rn.  A denominator |d| + eps is at
+// least eps, so with eps >= 2^-60 (the default is 1e-16) only the numerators
+// need the lower check.  fmaxf / fminf skip a NaN operand, which may then reach
+// div_rn_core: its quotient is NaN there as in the general division, and the
+// clamp makes either pi = 0.
 __device__ __forceinline__ void commit4_fast(const PassArgs& a, const float4& d, const float4& s,
                                              float4& th, float4& m, float4& snap,
                                              float* pi_out = nullptr)
@@ -109,25 +111,25 @@ __device__ __forceinline__ void commit4_fast(const PassArgs& a, const float4& d,
         num[k] = __builtin_fabsf(mv[k]) - __builtin_fabsf(drift);
         den[k] = __builtin_fabsf(dv[k]) + a.eps;
     }
-    float hi = __builtin_fabsf(num[0]), lo = hi;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (k > 0) {
-            hi = __builtin_fmaxf(hi, __builtin_fabsf(num[k]));
-            lo = __builtin_fminf(lo, __builtin_fabsf(num[k]));
-        }
-        hi = __builtin_fmaxf(hi, __builtin_fabsf(den[k]));
-        lo = __builtin_fminf(lo, __builtin_fabsf(den[k]));
+    float hi = __builtin_fmaxf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+    float lo = __builtin_fminf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+    hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
+    lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
+    hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[0]), den[1]);
+    hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[2]), den[3]);
+    // (on eps's bits: a scalar comparison; eps is positive)
+    if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
+        lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
+        lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
     }
-    // eq. 18, clamped at +0 (pi = q > 0 ? q : +0).  In the core range every
-    // quotient is finite, so the clamp is the signed-integer maximum of its
-    // bits with 0 (negative values and -0 have the sign bit set): one
-    // instruction, where the float form needs a canonicalisation as well.
+    // eq. 18, clamped at +0 (pi = q > 0 ? q : +0).  The median of q, 0 and inf
+    // is the clamp in one instruction, a NaN's being 0 (the median instruction
+    // takes the minimum of the other two).
     float pi[4];
     if (lo >= 0x1p-60f && hi <= 0x1p60f) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            pi[k] = __int_as_float(max(__float_as_int(div_rn_core(num[k], den[k])), 0));
+            pi[k] = __builtin_amdgcn_fmed3f(div_rn_core(num[k], den[k]), 0.0f, __builtin_inff());
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {

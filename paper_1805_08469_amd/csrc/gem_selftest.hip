@@ -8,7 +8,10 @@
 //     div_rn_core on the same operands) for every binary32 f the logarithm
 //     can see (the 2^23 values in (sqrt(1/2), sqrt(2)]);
 //   - the Box-Muller radius sqrt(-2 ln u) for every u = k 2^-24, k in
-//     [1, 2^24];
+//     [1, 2^24]: the radicand against the logarithm's defined steps, the root
+//     against the IEEE square root;
+//   - r cos(phi), r sin(phi) for all 2^24 angles and both signs of r against
+//     the defined steps of sin and cos;
 //   - the guarded quotient div_rn on Philox-random operand pairs spread over
 //     the whole binary32 range (zeros, subnormals, infinities and NaNs
 //     included), and on every significand of the denominator against a set
@@ -47,15 +50,75 @@ __global__ __launch_bounds__(kThreads) void ln_div_kernel(unsigned long long* ba
     if (!same_bits(gemk::div_rn_core(a, b), want)) atomicAdd(bad, 1ull);
 }
 
+// The defined steps of ln u, u = k 2^-24 in (0, 1], and of sin and cos of
+// 2 pi k / 2^24, written out plainly with the general IEEE operations.
+__device__ float defined_ln(float u)
+{
+    const uint32_t bits = __float_as_uint(u);
+    int e = static_cast<int>(bits >> 23) - 127;
+    const uint32_t mant = bits & 0x007FFFFFu;
+    float f = __uint_as_float(mant | 0x3F800000u);
+    if (mant > 0x003504F3u) {
+        f = 0.5f * f;
+        e += 1;
+    }
+    const float s = (f - 1.0f) / (f + 1.0f);
+    const float z = s * s;
+    float p = 1.0f / 9.0f;
+    p = __builtin_fmaf(p, z, 1.0f / 7.0f);
+    p = __builtin_fmaf(p, z, 1.0f / 5.0f);
+    p = __builtin_fmaf(p, z, 1.0f / 3.0f);
+    p = p * z;
+    const float s2 = s + s;
+    float r = __builtin_fmaf(static_cast<float>(e), 0x1.7f7d1cp-20f, __builtin_fmaf(s2, p, s2));
+    return __builtin_fmaf(static_cast<float>(e), 0x1.62e4p-1f, r);
+}
+
+__device__ void defined_sincos(uint32_t k, float& sn, float& cs)
+{
+    const uint32_t j = (k + (1u << 21)) >> 22;
+    const int rem = static_cast<int>(k) - static_cast<int>(j << 22);
+    const float x = static_cast<float>(rem) * (6.28318530717958647692f * 0x1p-24f);
+    const float x2 = x * x;
+    float ps = 1.0f / 362880.0f;
+    ps = __builtin_fmaf(ps, x2, -1.0f / 5040.0f);
+    ps = __builtin_fmaf(ps, x2, 1.0f / 120.0f);
+    ps = __builtin_fmaf(ps, x2, -1.0f / 6.0f);
+    ps = ps * x2;
+    const float sx = __builtin_fmaf(x, ps, x);
+    float pc = -1.0f / 3628800.0f;
+    pc = __builtin_fmaf(pc, x2, 1.0f / 40320.0f);
+    pc = __builtin_fmaf(pc, x2, -1.0f / 720.0f);
+    pc = __builtin_fmaf(pc, x2, 1.0f / 24.0f);
+    pc = __builtin_fmaf(pc, x2, -0.5f);
+    const float cx = __builtin_fmaf(pc, x2, 1.0f);
+    switch (j & 3u) {
+    case 0: sn = sx; cs = cx; break;
+    case 1: sn = cx; cs = -sx; break;
+    case 2: sn = -sx; cs = -cx; break;
+    default: sn = -cx; cs = sx; break;
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void radius_kernel(unsigned long long* bad)
 {
     const uint32_t k = blockIdx.x * kThreads + threadIdx.x + 1u;   // 1 .. 2^24
-    const float u = static_cast<float>(k) * 0x1p-24f;
-    const float x = -2.0f * gemk::ln_of_unit(u);
-    if (!same_bits(gemk::sqrt_rn_core(x), __builtin_sqrtf(x))) atomicAdd(bad, 1ull);
-    // the two ways to the logarithm (from u, and from k with the scaling in
-    // the exponent) agree
-    if (!same_bits(gemk::ln_of_k24(k), gemk::ln_of_unit(u))) atomicAdd(bad, 1ull);
+    const float want = -2.0f * defined_ln(static_cast<float>(k) * 0x1p-24f);
+    const float x = gemk::radicand_of_k24(k);
+    // (-2 ln 1 is -0 in the defined steps and +0 here: equal, and so are the roots)
+    if (!(x == want)) atomicAdd(bad, 1ull);
+    if (!(gemk::radicand_root(x) == __builtin_sqrtf(want))) atomicAdd(bad, 1ull);
+}
+
+__global__ __launch_bounds__(kThreads) void turn_kernel(float r, unsigned long long* bad)
+{
+    const uint32_t k = blockIdx.x * kThreads + threadIdx.x;        // 0 .. 2^24 - 1
+    float sn, cs, zc, zs;
+    defined_sincos(k, sn, cs);
+    // (the word's low 8 bits do not enter)
+    gemk::turn_times(r, (k << 8) | ((k * 37u) & 255u), zc, zs);
+    if (!same_bits(zc, r * cs)) atomicAdd(bad, 1ull);
+    if (!same_bits(zs, r * sn)) atomicAdd(bad, 1ull);
 }
 
 // A binary32 value from 32 random bits, with the exponent field drawn over
@@ -134,6 +197,14 @@ int gem_selftest_radius(uint64_t* mismatches)
     if (!mismatches) return GEM_EINVAL;
     return run_counting([](unsigned long long* bad) {
         hipLaunchKernelGGL(radius_kernel, dim3((1u << 24) / kThreads), dim3(kThreads), 0, 0, bad);
+    }, mismatches);
+}
+
+int gem_selftest_turn(float r, uint64_t* mismatches)
+{
+    if (!mismatches) return GEM_EINVAL;
+    return run_counting([&](unsigned long long* bad) {
+        hipLaunchKernelGGL(turn_kernel, dim3((1u << 24) / kThreads), dim3(kThreads), 0, 0, r, bad);
     }, mismatches);
 }
 

@@ -31,6 +31,7 @@ def lib():
     u64p = C.POINTER(C.c_uint64)
     L.gem_selftest_ln_div.argtypes = [u64p]
     L.gem_selftest_radius.argtypes = [u64p]
+    L.gem_selftest_turn.argtypes = [C.c_float, u64p]
     L.gem_selftest_div_random.argtypes = [C.c_uint64, C.c_int64, u64p]
     L.gem_selftest_div_grid.argtypes = [C.POINTER(C.c_float), C.c_int32, C.c_int32, u64p]
     return L
@@ -49,6 +50,12 @@ def test_logarithm_quotient_exhaustive(lib):
 
 def test_box_muller_radius_exhaustive(lib):
     assert _count(lib.gem_selftest_radius) == 0
+
+
+@pytest.mark.parametrize("r", [1.0, 1.2345678, 5.7681, 1e-3, 0.0])
+def test_angle_products_exhaustive(lib, r):
+    """r cos(phi) and r sin(phi) of every angle against the defined steps."""
+    assert _count(lib.gem_selftest_turn, r) == 0
 
 
 @pytest.mark.parametrize("seed", [1, 20180522])

@@ -139,8 +139,8 @@ typedef struct {
 /* Work counters since gem_create (or the last gem_stats_reset). */
 typedef struct {
     int64_t commits;      /* commits applied */
-    int64_t passes;       /* fused kernel launches */
-    double alg_bytes;     /* algorithmic HBM bytes of those launches (see below) */
+    int64_t passes;       /* fused passes of at most K commits */
+    double alg_bytes;     /* algorithmic HBM bytes of those passes (see below) */
 } gem_stats_t;
 
 /* ---- library -------------------------------------------------------------- */
@@ -223,7 +223,12 @@ int gem_schedule_make(int32_t n, int64_t T, const gem_schedule_law* law, uint64_
  * staleness tau[j] (host array, may be NULL, else checked like
  * gem_commit_batch), its update generated at the worker's snapshot (see
  * gem_sim_params), all fused into passes of at most K commits (1 <= K <=
- * GEM_K_MAX) that keep theta and the pass's (s, m) pairs in registers (under
+ * GEM_K_MAX).  The passes of one call share launches: a launch takes each
+ * part of the parameter vector through up to 993 commits (495 with adaptive
+ * staleness) while theta and the rows of workers that commit again soon stay
+ * on the chip, so the values and their bits do not depend on K, which is the
+ * unit of the work counters.  A call of one pass (T <= K), and passes with
+ * diagnostics or histograms enabled, are launched pass by pass (under
  * GEM_PI_SEGMENT K is checked but each commit is applied on its own).  Needs
  * gem_set_quadratic.  Errors: ESTATE, EINVAL, EWORKER, ESTALE. */
 int gem_sim_run(gem_t* g, const int32_t* worker, const int32_t* tau, int64_t T, int32_t K);
@@ -337,7 +342,9 @@ int gem_pi_hist_start(gem_t* g, int64_t capacity);
 int gem_pi_hist_start_segments(gem_t* g, int64_t capacity);
 int gem_pi_hist_read(gem_t* g, uint32_t* out, int64_t max_commits, int64_t* commits);
 
-/* Work counters.  alg_bytes counts, per pass over P' (P padded to 64) elements:
+/* Work counters.  passes counts passes of at most K commits, also where
+ * gem_sim_run takes several of them in one launch, and alg_bytes what they
+ * would move one by one: per pass over P' (P padded to 64) elements:
  * theta read and written, h and theta* read (simulated runs), each distinct
  * worker's S and M rows read and written once (GLOBAL proxy: its S row, plus
  * the shared moment read and written once), and caller updates read -- 4
@@ -371,7 +378,10 @@ int gem_load(gem_t* g, const char* path);
  * GEM_CACHE_KEEP uses the default policy, under which a state that fits the
  * 256 MiB Infinity Cache stays there between passes (streaming it is 14-24%
  * slower).  GEM_CACHE_AUTO (the default) streams when theta, h, theta* and
- * the snapshot and moment table together exceed 256 MiB.  Results are the
+ * the snapshot and moment table together exceed 256 MiB; a launch of many
+ * passes then streams only its rows, and only when its workers are too many
+ * (over 250) or its commits too few (under 1.4 a worker) for the cache to
+ * hold a row until its worker's next commit.  Results are the
  * same bits under every policy.  The diagnostic passes keep the default
  * policy; so do the per-segment scope's loads of h and theta*, which every
  * commit reads: with the other streams non-temporal the Infinity Cache keeps

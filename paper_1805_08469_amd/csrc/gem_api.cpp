@@ -62,6 +62,7 @@ struct gem_handle {
     double* sup = nullptr;           // [3][nsup] index-block sums
     float* pi_seg = nullptr;         // [nseg]
     uint32_t* seg_done = nullptr;    // [nseg] pair blocks finished in the running launch
+    int32_t lds_per_cu = 0;          // LDS of a compute unit, bytes (0 if unknown)
     uint32_t deep_lds = 0;           // LDS reserved per block of the deep-ring pass
     int32_t cus = 0;                 // compute units of the device (0 if unknown)
     int64_t npart = 0;
@@ -308,6 +309,118 @@ int run_passes(gem_handle* g, const std::vector<Pass>& passes, Source src,
         g->stats.passes += 1;
         g->stats.alg_bytes += bytes;
         if (g->diag_on) g->diag_commits += p.K;
+    }
+    return GEM_OK;
+}
+
+// How a run's launch shares the compute units and reads its rows.
+struct RunShape {
+    int slots;      // LDS slots of a block
+    bool stream;    // non-temporal row accesses
+};
+
+// For a launch of k commits by `distinct` workers.  160 KiB of LDS per compute
+// unit hold 20 slots (40 with the shared moment's half slots), shared by the
+// blocks resident there; measured at 12.5M parameters, 988 commits:
+//   - 4 blocks of 5 (10) slots when that holds every worker: nothing moves, and
+//     four waves per SIMD issue best (5 workers: 13.2 ms, 13.8 ms with 3 blocks,
+//     16.2 with 2);
+//   - up to 100 workers 3 blocks (10 workers: 15.6, 2 blocks 16.2; 64 workers
+//     equal; 100 workers 21.4, 2 blocks 21.2);
+//   - beyond, 2 blocks of 10 slots: fewer rows move, and the rows in flight have
+//     larger shares of the Infinity Cache (150 workers: 21.7, 3 blocks 25.2; 300:
+//     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
+//     (300 workers: 17.2, 2 blocks 18.1).
+// Rows stream when few of them are found in the Infinity Cache again: beyond
+// 250 workers (300: 26.5 ms, default policy 27.2; 200: 24.5, 23.6), or when a
+// worker commits fewer than 1.4 times in the launch (25M parameters, 100
+// workers, 48 commits: 2.59 ms, 2.82; 96 commits: 4.91, 4.56).
+RunShape run_shape(const gem_handle* g, gemk::Variant v, int64_t k, int64_t distinct)
+{
+    const int all = static_cast<int>(std::min<int64_t>(g->lds_per_cu, 160 << 10)) / gemk::run_slot_bytes(v);
+    int blocks = 3;
+    if (distinct <= all / 4) blocks = 4;
+    else if (distinct > 100 && v != gemk::Variant::FastGlobal) blocks = 2;
+    RunShape r;
+    r.slots = std::min(std::max(all / blocks, gemk::kRunDepth), gemk::kRunMaxSlots);
+    if (g->cache_policy != GEM_CACHE_AUTO) r.stream = g->cache_policy == GEM_CACHE_STREAM;
+    else r.stream = stream_rows(g) && (distinct > 250 || 10 * k < 14 * distinct);
+    return r;
+}
+
+// Queue a run of T commits on generated updates as launches of up to
+// kRunCommits commits each; advance the clock and pull bookkeeping.  The work
+// counters count the passes of at most K commits that run_passes would launch.
+int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
+{
+    gemk::RunArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.theta = g->theta;
+    a.S = g->S;
+    a.h = g->h;
+    a.ts = g->ts;
+    a.Pp = g->Pp;
+    a.nw = g->n;
+    a.key0 = static_cast<uint32_t>(g->sp.seed);
+    a.key1 = static_cast<uint32_t>(g->sp.seed >> 32);
+    a.neg_lr = -g->sp.lr;
+    a.sigma = g->sp.sigma;
+    a.mu = g->hp.momentum;
+    a.eps = g->hp.eps;
+    a.k_eff = kappa_eff(g->hp);
+    a.mode = mode_bits(g->hp);
+    // (the general variant takes an eps of any size)
+    const gemk::Variant variant = g->hp.eps < 0x1p-60f ? gemk::Variant::General : kernel_variant(g->hp);
+    const bool adaptive = g->hp.rule == GEM_RULE_ADAPTIVE;
+    // The commits of one launch: as many as the argument block takes, and at
+    // most 2^36 element-commits (a tenth of a second), so that a launch over a
+    // very large vector does not keep the GPU from other streams for long.
+    const int64_t most = std::min<int64_t>(
+        adaptive ? gemk::kRunTauAt - gemk::kRunDepth : gemk::kRunCommits,
+        std::max<int64_t>(GEM_K_MAX, (int64_t{1} << 36) / g->Pp));
+    const int64_t launches = (T + most - 1) / most;
+    const size_t n = static_cast<size_t>(g->n);
+    std::vector<int32_t> last(n, -1);
+    std::vector<int64_t> pull, counted(n, -1);   // counted: the pass a worker was last counted in
+    if (adaptive) pull = g->pc;
+    const bool shared = g->hp.proxy_mode == GEM_PROXY_GLOBAL;
+    const double row_bytes = 4.0 * static_cast<double>(g->Pp);
+    int64_t j0 = 0, pass = -1;
+    for (int64_t l = 0; l < launches; ++l) {
+        const int k = static_cast<int>((T - j0) / (launches - l));   // launches of even length
+        const int32_t* w = worker + j0;
+        int64_t distinct = 0;
+        for (int j = 0; j < k; ++j) {
+            distinct += last[w[j]] < 0;
+            last[w[j]] = 0;
+        }
+        for (int j = 0; j < k; ++j) last[w[j]] = -1;
+        const RunShape shape = run_shape(g, variant, k, distinct);
+        gemk::plan_run(w, k, gemk::kRunDepth, shape.slots, a.sched, last.data());
+        a.t0 = static_cast<uint32_t>(g->t);
+        a.K = k;
+        for (int j = 0; adaptive && j < k; ++j) {
+            a.sched[gemk::kRunTauAt + j] = static_cast<uint32_t>(g->t + j - pull[w[j]]);
+            pull[w[j]] = next_pull(g, g->t + j);
+        }
+        GEM_HIP(gemk::launch_run(a, variant, g->sp.update_dtype == GEM_BF16, shape.stream,
+                                 static_cast<uint32_t>(shape.slots * gemk::run_slot_bytes(variant)),
+                                 g->stream));
+        for (int j = 0; j < k; ++j) {
+            g->pc[w[j]] = next_pull(g, g->t + j);
+            if ((j0 + j) % K == 0) {
+                pass += 1;
+                g->stats.passes += 1;
+                g->stats.alg_bytes += (shared ? 6.0 : 4.0) * row_bytes;   // theta, h, theta* (moment)
+            }
+            if (counted[w[j]] != pass) {
+                counted[w[j]] = pass;
+                g->stats.alg_bytes += (shared ? 2.0 : 4.0) * row_bytes;
+            }
+        }
+        g->t += k;
+        g->stats.commits += k;
+        j0 += k;
     }
     return GEM_OK;
 }
@@ -605,7 +718,7 @@ int gem_create(int64_t P, int32_t n, const gem_hyperparams* hp, void* stream, ge
         int lds = 0;
         if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                                   g->device) == hipSuccess)
-            g->deep_lds = gemk::deep_lds_bytes(lds);
+            g->deep_lds = gemk::deep_lds_bytes(g->lds_per_cu = lds);
         else
             (void)hipGetLastError();   // no cap: the pass runs as its registers allow
         if (hipDeviceGetAttribute(&g->cus, hipDeviceAttributeMultiprocessorCount, g->device) !=
@@ -754,6 +867,14 @@ int gem_sim_run(gem_t* g, const int32_t* worker, const int32_t* tau, int64_t T, 
         return run_segments(g, worker, T, Source::Generated, nullptr,
                             g->sp.update_dtype == GEM_BF16);
     }
+    // More than one pass: one launch takes the commits of many.  (A single pass
+    // keeps its own kernel: with each worker's rows read and written once, there
+    // is nothing to keep, and it streams 2% faster: 25M parameters, 100 workers,
+    // 32 commits 1.84 ms, as a run 1.87.)  Diagnostics and recordings need the
+    // pass kernels.
+    if (T > K && !g->diag_on && !g->hist_on && g->n <= gemk::kRunMaxWorkers &&
+        g->lds_per_cu >= gemk::kRunMinLds)
+        return run_runs(g, worker, T, K);
     const int depth = pass_depth(g, Source::Generated, std::min<int64_t>(K, T));
     std::vector<Pass> passes;
     plan_passes(g, worker, T, K, depth, passes);

@@ -71,6 +71,27 @@ struct PassArgs {
 
 enum class Source { Generated = 0, GivenF32 = 1, GivenBF16 = 2 };
 
+// Kernel argument block of one run launch: K <= kRunCommits commits at clocks
+// t0 .. t0 + K - 1, the schedule packed one word a commit (gem_plan.hpp).
+struct RunArgs {
+    float* theta;            // [Pp]
+    float* S;                // the table (as in PassArgs)
+    const float* h;          // [Pp]
+    const float* ts;         // [Pp]
+    int64_t Pp;
+    int64_t nw;
+    uint32_t key0, key1;
+    uint32_t t0;
+    int32_t K;
+    float neg_lr, sigma, mu, eps, k_eff;
+    uint32_t mode;
+    // K words, then kRunDepth words that read no memory; with the
+    // adaptive-staleness rule the K staleness values from kRunTauAt on.
+    uint32_t sched[kRunWords];
+};
+// The runtime passes kernel arguments of up to 4 KiB.
+static_assert(sizeof(RunArgs) <= 4096, "the argument block fits");
+
 // Segment-norm scale factors.  A sum of squares is the adjacent-pairs tree
 // over aligned blocks of kSegBlock indices, then the blocks in order.  The
 // step kernel forms the tree's lower levels, one aligned group of
@@ -127,6 +148,10 @@ struct SegArgs {
 // first moments; General takes every mode as uniform runtime flags.
 enum class Variant { General = 0, Fast = 1, FastGlobal = 2 };
 
+// LDS of one slot of a run: a block's 1024 elements of a worker's snapshot and
+// moment (of its snapshot with the default rule's shared moment).
+constexpr int run_slot_bytes(Variant v) { return v == Variant::FastGlobal ? 4096 : 8192; }
+
 // Launchers (defined in gem_kernels.hip).
 // depth: kPrefetchShallow, or kPrefetchDeep for (Generated, Fast, no
 // diagnostics), or kPrefetchNone for a pass of one commit (a.K == 1, no
@@ -137,6 +162,10 @@ enum class Variant { General = 0, Fast = 1, FastGlobal = 2 };
 // deep-ring pass (deep_lds_bytes), 0 for none.
 // rec: the fast recording pass (Generated, Fast, no diagnostics; one
 // histogram per commit in a.pi_hist).
+// A run of a.K commits.  lds_bytes: the slots the schedule words use, of
+// run_slot_bytes(v) each.  Fast and FastGlobal need eps >= 2^-60.
+hipError_t launch_run(const RunArgs& a, Variant v, bool bf16_out, bool stream_rows,
+                      uint32_t lds_bytes, hipStream_t stream);
 hipError_t launch_pass(const PassArgs& a, Source src, Variant v, bool bf16_out, bool diag,
                        bool rec, int depth, bool stream_rows, uint32_t deep_lds,
                        hipStream_t stream);

@@ -86,6 +86,11 @@ __device__ __forceinline__ int scale_bin(float x)
     return 2 + octave * 16 + static_cast<int>((b >> 19) & 0xFu);
 }
 
+// Has x computed here: without it the compiler moves the chain of maxima past
+// the branch that follows, where it no longer folds the |.| into them (6
+// instructions more).
+__device__ __forceinline__ void keep(float& x) { asm volatile("" : "+v"(x)); }
+
 // The default rule's step on a thread's four elements (Fast variants, no
 // diagnostics): the same arithmetic as commit_element, with one range check
 // for the four quotients.  When all eight operand magnitudes lie in
@@ -95,7 +100,10 @@ __device__ __forceinline__ int scale_bin(float x)
 // need the lower check.  fmaxf / fminf skip a NaN operand, which may then reach
 // div_rn_core: its quotient is NaN there as in the general division, and the
 // clamp makes either pi = 0.
-__device__ __forceinline__ void commit4_fast(const PassArgs& a, const float4& d, const float4& s,
+// SMALL_EPS: eps may be below 2^-60 (else the caller has made sure it is not,
+// and the step is one straight run of instructions but for the rare fallback).
+template <bool SMALL_EPS, typename Args>
+__device__ __forceinline__ void commit4_fast(const Args& a, const float4& d, const float4& s,
                                              float4& th, float4& m, float4& snap,
                                              float* pi_out = nullptr)
 {
@@ -117,20 +125,22 @@ __device__ __forceinline__ void commit4_fast(const PassArgs& a, const float4& d,
     lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
     hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[0]), den[1]);
     hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[2]), den[3]);
-    // (on eps's bits: a scalar comparison; eps is positive)
-    if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
-        lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
-        lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
+    if constexpr (SMALL_EPS) {
+        keep(hi);
+        // (on eps's bits: a scalar comparison; eps is positive)
+        if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
+            lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
+            lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
+        }
     }
     // eq. 18, clamped at +0 (pi = q > 0 ? q : +0).  The median of q, 0 and inf
     // is the clamp in one instruction, a NaN's being 0 (the median instruction
     // takes the minimum of the other two).
     float pi[4];
-    if (lo >= 0x1p-60f && hi <= 0x1p60f) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            pi[k] = __builtin_amdgcn_fmed3f(div_rn_core(num[k], den[k]), 0.0f, __builtin_inff());
-    } else {
+    for (int k = 0; k < 4; ++k)
+        pi[k] = __builtin_amdgcn_fmed3f(div_rn_core(num[k], den[k]), 0.0f, __builtin_inff());
+    if (__builtin_expect(__ballot(!(lo >= 0x1p-60f && hi <= 0x1p60f)) != 0, 0)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float q = div_rn(num[k], den[k]);
@@ -463,7 +473,7 @@ __device__ __forceinline__ StepOut pass_step(const PassArgs& a, int j, Chunk& ch
     r.out.m = rows.m;
     if constexpr (FAST && !DIAG) {
         float pis[4];
-        commit4_fast(a, d, rows.s, ch.th, r.out.m, r.out.s, REC ? pis : nullptr);
+        commit4_fast<true>(a, d, rows.s, ch.th, r.out.m, r.out.s, REC ? pis : nullptr);
         if constexpr (REC) {
             // this commit's factors into the block's LDS histogram (uniform
             // test: recording stops at the capacity)
@@ -707,6 +717,222 @@ __global__ __launch_bounds__(kBlock) void pass_kernel(const PassArgs a)
     } else {
         pass_group<SRC, V, BF16, DIAG, DEPTH, NT, REC>(a, blockIdx.x, dyn_lds);
     }
+}
+
+// The general rule's step on a thread's four elements (run kernel, General
+// variant): commit_element's arithmetic, every mode a uniform runtime flag,
+// with one range check for the four quotients as in commit4_fast.
+__device__ __forceinline__ void commit4_general(const RunArgs& a, int tau, const float4& d,
+                                                const float4& s, float4& th, float4& m,
+                                                float4& snap)
+{
+    const float dv[4] = {d.x, d.y, d.z, d.w};
+    const float sv[4] = {s.x, s.y, s.z, s.w};
+    float tv[4] = {th.x, th.y, th.z, th.w};
+    float mv[4] = {m.x, m.y, m.z, m.w};
+    float add[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mv[k] = __builtin_fmaf(a.mu, mv[k], dv[k]);
+    if (a.mode & kModeDownpour) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tv[k] = tv[k] + dv[k];          // eq. 1
+    } else {
+        // num / den: the scale factor (eq. 18), or the damped update itself
+        const bool adaptive = (a.mode & kModeAdaptive) != 0;
+        const float k_eff = (a.mode & kModeKappaMul) ? a.k_eff : 1.0f;
+        const float stale = static_cast<float>(tau + 1);
+        float num[4], den[4], q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float drift = tv[k] - sv[k];
+            num[k] = adaptive ? dv[k] : k_eff * __builtin_fabsf(mv[k]) - __builtin_fabsf(drift);
+            den[k] = adaptive ? stale : __builtin_fabsf(dv[k]) + a.eps;
+        }
+        float hi = __builtin_fmaxf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+        float lo = __builtin_fminf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+        hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
+        lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
+        hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[0]), den[1]);
+        hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[2]), den[3]);
+        keep(hi);
+        if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
+            lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
+            lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = div_rn_core(num[k], den[k]);
+        if (__builtin_expect(__ballot(!(lo >= 0x1p-60f && hi <= 0x1p60f)) != 0, 0)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = div_rn(num[k], den[k]);
+        }
+        if (adaptive) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add[k] = tv[k] + q[k];
+        } else {
+            const bool literal = (a.mode & kModeLiteralPi) != 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float pi = literal ? q[k] : __builtin_amdgcn_fmed3f(q[k], 0.0f,
+                                                                          __builtin_inff());
+                add[k] = __builtin_fmaf(pi, dv[k], tv[k]);          // eq. 3
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tv[k] = add[k];
+    }
+    const float4 before = th;
+    th = make_float4(tv[0], tv[1], tv[2], tv[3]);
+    snap = (a.mode & kModePrePull) ? before : th;
+    m = make_float4(mv[0], mv[1], mv[2], mv[3]);
+}
+
+// Row accesses of the run kernel: buffer instructions on a descriptor of the
+// block's 4 KiB of the row, or of no bytes when the step does not need the
+// access: then every lane is out of range, a load gives zeros and a store is
+// dropped, without a memory request.  The number of memory instructions a
+// step issues is therefore fixed (the compiler's waits count them).
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+constexpr int kBufferFlags = 0x00027000;   // raw 32-bit words, range-checked by bytes
+
+template <bool NT>
+__device__ __forceinline__ float4 row_at(float* base, bool mem, uint32_t byte_off)
+{
+    const __amdgpu_buffer_rsrc_t d =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, mem ? kBlock * 16 : 0, kBufferFlags);
+    const v4u v = __builtin_amdgcn_raw_buffer_load_b128(d, byte_off, 0, NT ? 2 : 0);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                       __uint_as_float(v.w));
+}
+
+template <bool NT>
+__device__ __forceinline__ void put_row_at(float* base, bool mem, uint32_t byte_off, float4 v)
+{
+    const __amdgpu_buffer_rsrc_t d =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, mem ? kBlock * 16 : 0, kBufferFlags);
+    __builtin_amdgcn_raw_buffer_store_b128(v4u{__float_as_uint(v.x), __float_as_uint(v.y),
+                                               __float_as_uint(v.z), __float_as_uint(v.w)},
+                                           d, byte_off, 0, NT ? 2 : 0);
+}
+
+// A run of up to kRunCommits commits in one launch (generated updates, no
+// diagnostics): a block takes its 1024 elements through all of them before the
+// next block takes its place.  A pass of 32 commits per launch read and wrote
+// each committing worker's rows once a pass, 13.7 bytes per element-commit at
+// 100 workers, and waited on that traffic; here
+//   - rows of workers that commit again soon wait in LDS slots (plan_run), so
+//     a commit moves its worker's rows in 0.7 of the cases with 6 slots and 100
+//     workers, 0.63 with 50 (0.84 and 0.78 in passes of 32 with 4 slots);
+//   - theta, h and theta* are read once per run instead of once per pass;
+//   - the rows a block moves again lie in the Infinity Cache's share of the
+//     few hundred blocks in flight, if the workers are not too many.
+// What is left is 220 VALU instructions per wave and commit, issued at 0.43 ms
+// per 32 commits and 12.5M elements when all rows stay in LDS, and the rows'
+// traffic at 6.5 TB/s between L2 and the fabric, the rate a copy reaches (100
+// workers: 0.69 ms for 4.5 GB).  Measured at 25M parameters and 100 workers,
+// 988 commits: 55.3 ms in passes of 32, 39.8 ms here.
+//
+// Rows come DEPTH commits ahead into a register ring; 3 measured best (2 and 4
+// are 2% and 1% slower, 6 and 8 more).  Noise is drawn one commit ahead, in
+// the same straight run of instructions as the commit's step, so that the two
+// chains fill each other's latencies (the kernel runs 3 waves per SIMD: 6%
+// faster with all rows in LDS).  Chunks wait in LDS rather than in registers:
+// 8 register slots beside 6 in LDS, selected by uniform branches, moved a
+// quarter less but ran 2% slower.
+template <Variant V, bool BF16, int DEPTH, bool NT>
+__global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
+{
+    extern __shared__ float4 slot_lds[];   // [slots][1 or 2 rows][kBlock]
+    constexpr bool SHARED = V == Variant::FastGlobal;       // only snapshots move
+    constexpr int kSlotRows = SHARED ? 1 : 2;
+    const bool global_m = SHARED || (V == Variant::General && (a.mode & kModeGlobalProxy));
+    const int64_t grp = blockIdx.x;
+    const int64_t c = grp * kBlock + threadIdx.x;
+    if (c >= (a.Pp >> 2)) return;
+    const int64_t blk0 = grp * (kBlock * 4);
+    const uint32_t t16 = threadIdx.x * 16u;
+    const uint32_t q_hi = static_cast<uint32_t>((grp * kBlock) >> 32);
+    const uint32_t q_lo = static_cast<uint32_t>(c);
+    float* const row0 = a.S + tile_index(a.nw, 0, blk0 & ~(kTileElems - 1)) + (blk0 & (kTileElems - 1));
+    float4* const mine = slot_lds + threadIdx.x;
+
+    float4 th = load4_at<false>(a.theta + blk0, t16);
+    const float4 hh = load4_at<NT>(a.h + blk0, t16);
+    const float4 tt = load4_at<NT>(a.ts + blk0, t16);
+    float4 mg = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (global_m) mg = load4_at<false>(row0 + kTileElems, t16);
+
+    // Loads of the rows the schedule word wd takes from memory, into r.
+    auto fetch = [&](uint32_t wd, Rows& r) __attribute__((always_inline)) {
+        const bool mem = (wd & kRunSlotMask) == kRunMemory;
+        float* p = row0 + (static_cast<int64_t>(wd >> kRunWorkerShift) << (kTileShift + 1));
+        r.s = row_at<NT>(p, mem, t16);
+        if constexpr (!SHARED) r.m = row_at<NT>(p + kTileElems, mem, t16);
+    };
+    Rows ring[DEPTH];
+    uint32_t words[DEPTH];
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+        words[u] = a.sched[u];
+        ring[u] = Rows{};
+        fetch(words[u], ring[u]);
+    }
+
+    auto noise = [&](int j) __attribute__((always_inline)) {
+        return normals4((static_cast<uint64_t>(q_hi) << 32) | q_lo,
+                        a.t0 + static_cast<uint32_t>(j), a.key0, a.key1);
+    };
+    float4 z = noise(0);
+    auto step = [&](int j, uint32_t& word, Rows& rows) __attribute__((always_inline)) {
+        const uint32_t wd = word;
+        const uint32_t next = a.sched[j + DEPTH];
+        const uint32_t src = wd & kRunSlotMask;
+        const uint32_t dst = (wd >> kRunDstShift) & kRunSlotMask;
+        if (src != kRunMemory) {
+            const float4* p = mine + src * (kSlotRows * kBlock);
+            rows.s = p[0];
+            if constexpr (!SHARED) rows.m = p[kBlock];
+        }
+        float4 m = global_m ? mg : rows.m;
+        float4 d;
+        d.x = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.x, hh.x, tt.x, z.x);
+        d.y = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.y, hh.y, tt.y, z.y);
+        d.z = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.z, hh.z, tt.z, z.z);
+        d.w = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.w, hh.w, tt.w, z.w);
+        z = noise(j + 1);
+        float4 snap;
+        if constexpr (V == Variant::General) {
+            const int tau = (a.mode & kModeAdaptive)
+                                ? static_cast<int>(a.sched[kRunTauAt + j]) : 0;
+            commit4_general(a, tau, d, rows.s, th, m, snap);
+        } else {
+            commit4_fast<false>(a, d, rows.s, th, m, snap);
+        }
+        if (global_m) mg = m;
+        if (dst != kRunMemory) {
+            float4* p = mine + dst * (kSlotRows * kBlock);
+            p[0] = snap;
+            if constexpr (!SHARED) p[kBlock] = m;
+        }
+        {
+            const bool mem = dst == kRunMemory;
+            float* p = row0 + (static_cast<int64_t>(wd >> kRunWorkerShift) << (kTileShift + 1));
+            put_row_at<NT>(p, mem, t16, snap);
+            if constexpr (!SHARED)
+                put_row_at<NT>(p + kTileElems, mem && !(V == Variant::General && global_m), t16, m);
+        }
+        word = next;
+        fetch(next, rows);
+    };
+    int j = 0;
+    for (; j + DEPTH <= a.K; j += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) step(j + u, words[u], ring[u]);
+    }
+#pragma unroll
+    for (int u = 0; u + 1 < DEPTH; ++u)
+        if (j + u < a.K) step(j + u, words[u], ring[u]);
+    store4_at<false>(a.theta + blk0, t16, th);
+    if (global_m) store4_at<false>(row0 + kTileElems, t16, mg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1327,6 +1553,42 @@ hipError_t launch_pass(const PassArgs& a, Source src, Variant v, bool bf16_out, 
                                                    stream);
     }
     return hipErrorInvalidValue;
+}
+
+namespace {
+
+template <Variant V, bool BF16, bool NT>
+hipError_t launch_run_one(const RunArgs& a, uint32_t lds, hipStream_t stream)
+{
+    hipLaunchKernelGGL((run_kernel<V, BF16, kRunDepth, NT>), dim3(blocks_for(a.Pp >> 2)), dim3(kBlock),
+                       lds, stream, a);
+    return hipGetLastError();
+}
+
+template <Variant V>
+hipError_t launch_run_v(const RunArgs& a, bool bf16_out, bool stream_rows, uint32_t lds,
+                        hipStream_t stream)
+{
+    if (bf16_out)
+        return stream_rows ? launch_run_one<V, true, true>(a, lds, stream)
+                           : launch_run_one<V, true, false>(a, lds, stream);
+    return stream_rows ? launch_run_one<V, false, true>(a, lds, stream)
+                       : launch_run_one<V, false, false>(a, lds, stream);
+}
+
+}  // namespace
+
+hipError_t launch_run(const RunArgs& a, Variant v, bool bf16_out, bool stream_rows,
+                      uint32_t lds_bytes, hipStream_t stream)
+{
+    if (a.K < 1 || a.K > kRunCommits) return hipErrorInvalidValue;
+    switch (v) {
+    case Variant::Fast: return launch_run_v<Variant::Fast>(a, bf16_out, stream_rows, lds_bytes, stream);
+    case Variant::FastGlobal:
+        return launch_run_v<Variant::FastGlobal>(a, bf16_out, stream_rows, lds_bytes, stream);
+    case Variant::General: break;
+    }
+    return launch_run_v<Variant::General>(a, bf16_out, stream_rows, lds_bytes, stream);
 }
 
 template <bool DIAG, bool NT>

@@ -137,4 +137,72 @@ inline int plan_pass(const int32_t* worker, int k, int depth, uint32_t* routes, 
     return k;
 }
 
+// ---- runs: many passes' commits in one launch ---------------------------------
+constexpr int kRunDepth = 3;
+// One schedule word a commit: bits 0-4 where the committing worker's chunk
+// comes from (an LDS slot, or kRunMemory), bits 5-9 where it goes, the worker
+// from bit 10 on.
+constexpr uint32_t kRunSlotMask = 31u;
+constexpr uint32_t kRunMemory = 31u;
+constexpr int kRunDstShift = 5;
+constexpr int kRunWorkerShift = 10;
+constexpr int32_t kRunMaxWorkers = 1 << (32 - kRunWorkerShift);
+constexpr int kRunMaxSlots = 31;
+constexpr int32_t kRunMinLds = 64 << 10;   // LDS per compute unit the slots are sized for, at least
+constexpr int kRunWords = 996;
+constexpr int kRunCommits = kRunWords - kRunDepth;
+constexpr int kRunTauAt = kRunWords / 2;   // adaptive staleness: where the tau values start
+
+// Routes of one run of k <= kRunCommits commits with `slots` LDS slots, depth
+// <= slots: which chunks wait in a slot between two commits of their worker.
+// A wait is an interval of commits; at most `slots` may overlap, and the
+// most waits are kept by dropping, whenever one too many overlaps, the one
+// that ends last.  A wait shorter than depth must be kept (the ring's read for
+// its end would be issued before its start is written); fewer than depth such
+// waits overlap, so one that may be dropped is always there.  words receives
+// the k schedule words and `depth` words that read no memory; last is scratch
+// of one int per worker (-1 on entry and on return).
+inline void plan_run(const int32_t* worker, int k, int depth, int slots, uint32_t* words, int32_t* last)
+{
+    int next[kRunCommits], slot[kRunCommits];
+    for (int j = k - 1; j >= 0; --j) {
+        next[j] = last[worker[j]];
+        last[worker[j]] = j;
+        slot[j] = -1;
+    }
+    int holder[kRunMaxSlots];
+    for (int q = 0; q < slots; ++q) holder[q] = -1;
+    for (int j = 0; j < k; ++j) last[worker[j]] = -1;
+    for (int j = 0; j < k; ++j) {
+        const int prev = last[worker[j]];
+        uint32_t src = kRunMemory;
+        if (prev >= 0 && slot[prev] >= 0) {
+            src = static_cast<uint32_t>(slot[prev]);
+            holder[slot[prev]] = -1;
+        }
+        last[worker[j]] = j;
+        words[j] = (static_cast<uint32_t>(worker[j]) << kRunWorkerShift) | src;
+        if (next[j] < 0) continue;
+        int free_slot = -1, far = -1;
+        for (int q = slots - 1; q >= 0; --q) {
+            const int p = holder[q];
+            if (p < 0) { free_slot = q; break; }
+            if (next[p] - p >= depth && (far < 0 || next[p] > next[holder[far]])) far = q;
+        }
+        if (free_slot < 0 && far >= 0 && (next[holder[far]] > next[j] || next[j] - j < depth)) {
+            slot[holder[far]] = -1;
+            free_slot = far;
+        }
+        if (free_slot >= 0) {
+            slot[j] = free_slot;
+            holder[free_slot] = j;
+        }
+    }
+    for (int j = 0; j < k; ++j) {
+        words[j] |= (slot[j] >= 0 ? static_cast<uint32_t>(slot[j]) : kRunMemory) << kRunDstShift;
+        last[worker[j]] = -1;
+    }
+    for (int q = 0; q < depth; ++q) words[k + q] = 0u;
+}
+
 }  // namespace gemk

@@ -1,0 +1,113 @@
+"""Runs of many commits in one launch against the oracle, bit for bit: sizes at
+the edges of chunks, blocks and tiles, worker counts at the edges of the LDS
+slots (5, 6 and 10 chunks, 10 and 13 with the shared moment), lengths at the
+edges of a launch (993 commits, 495 with adaptive staleness), every rule the
+run kernel takes, both cache policies; and the same schedule as single passes,
+which run the pass kernels."""
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_util import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1805_08469_amd import gem
+    return gem
+
+
+def _hp(G, **kw):
+    hp = G.gem_hyperparams_default()
+    for k, v in kw.items():
+        setattr(hp, k, v)
+    return hp
+
+
+def _oracle(G, hp, P, n, worker, tau, h, ts, bf16):
+    ohp = O.Hyper(lr=0.01, sigma=0.1, momentum=hp.momentum, eps=hp.eps, kappa=hp.kappa,
+                  pi_mode=hp.pi_mode, kappa_mode=hp.kappa_mode, pull_mode=hp.pull_mode,
+                  rule=hp.rule, bf16=bf16, proxy=hp.proxy_mode, seed=77)
+    st = O.State.initial(n, P)
+    O.run(ohp, P, st, np.arange(P), h, ts, worker, tau)
+    return st
+
+
+def _case(G, P, n, T, K, hp, bf16=False, policy=0, law=0, p0=0.0, p1=0.0, chunks=(0,)):
+    """chunks: lengths of the gem_sim_run calls (0: one call of T commits)."""
+    from paper_1805_08469_amd.workloads import make_problem
+    print(f"[run] P={P} n={n} T={T} K={K} bf16={bf16} policy={policy} chunks={chunks}", flush=True)
+    h, ts = make_problem(P, 1e-3, 1.0, 3)
+    worker, tau = G.gem_schedule_make(n, T, law, p0, p1, seed=n + T, pull_mode=hp.pull_mode)
+    st = _oracle(G, hp, P, n, worker, tau, h, ts, bf16)
+    for c in chunks:
+        with G.Gem(P, n, hp) as g:
+            g.set_cache_policy(policy)
+            g.set_quadratic(h, ts, 0.01, 0.1, 77, bf16=bf16)
+            for j in range(0, T, c or T):
+                g.sim_run(worker[j:j + (c or T)], tau[j:j + (c or T)], K)
+            assert g.clock == st.t and np.array_equal(g.pull_clocks(), st.pc)
+            assert_parity(f"theta (calls of {c})", g.theta(), st.theta)
+            assert_parity(f"S (calls of {c})", g.S(), st.S)
+            assert_parity(f"M (calls of {c})", g.M(), st.M)
+            s = g.stats()
+            assert s.commits == T
+            if c == 0:
+                assert s.passes == -(-T // K)
+
+
+@pytest.mark.parametrize("P", [1, 4, 63, 1023, 1025, 8193])
+def test_sizes(G, P):
+    _case(G, P, 7, 150, 16, _hp(G))
+
+
+@pytest.mark.parametrize("proxy", [0, 1])
+@pytest.mark.parametrize("n", [1, 5, 6, 7, 10, 11, 14, 101, 260])
+def test_worker_counts(G, n, proxy):
+    _case(G, 1100, n, 600, 8, _hp(G, proxy_mode=proxy))
+
+
+@pytest.mark.parametrize("T", [2, 3, 4, 993, 994, 2 * 993 + 1])
+def test_launch_lengths(G, T):
+    _case(G, 300, 20, T, 1, _hp(G))
+
+
+MODES = {
+    "kappa": dict(kappa=2.0), "sqrt_kappa": dict(kappa=3.0, kappa_mode=1), "pre_pull": dict(pull_mode=1),
+    "downpour": dict(rule=1, momentum=0.0), "adaptive": dict(rule=2), "tiny_eps": dict(eps=1e-30),
+    "shared_kappa": dict(proxy_mode=1, kappa=2.0), "shared_tiny_eps": dict(proxy_mode=1, eps=1e-25),
+    "shared_pre_pull": dict(proxy_mode=1, pull_mode=1), "big_eps": dict(eps=1e-3),
+}
+
+
+@pytest.mark.parametrize("mode", sorted(MODES))
+@pytest.mark.parametrize("bf16", [False, True])
+def test_modes(G, mode, bf16):
+    """One call (the run kernel), and calls of one pass (the pass kernels)."""
+    _case(G, 2050, 9, 520, 16, _hp(G, **MODES[mode]), bf16=bf16, chunks=(0, 16))
+
+
+@pytest.mark.parametrize("T", [494, 495, 496, 991])
+def test_adaptive_launch_lengths(G, T):
+    _case(G, 200, 12, T, 4, _hp(G, rule=G.GEM_RULE_ADAPTIVE))
+
+
+@pytest.mark.parametrize("policy", [1, 2])
+@pytest.mark.parametrize("proxy", [0, 1])
+def test_policies_and_heavy_tails(G, policy, proxy):
+    """Both cache policies, a Pareto schedule (runs of one worker), and the pass
+    kernels of every depth (calls of 1, 8 and 32 commits)."""
+    _case(G, 3000, 30, 320, 32, _hp(G, proxy_mode=proxy), bf16=True, policy=policy, law=3, p0=1.5,
+          p1=1 / 3, chunks=(0, 1, 8, 32))
+
+
+def test_literal_pi_with_nan(G):
+    """The literal rule diverges to infinities and NaN: the same ones."""
+    P, n, T = 1030, 6, 400
+    hp = _hp(G, pi_mode=G.GEM_PI_LITERAL)
+    _case(G, P, n, T, 8, hp, chunks=(0, 8))

@@ -1379,13 +1379,30 @@ __global__ __launch_bounds__(kBlock) void fill_rows_kernel(float* base, int64_t 
 }
 
 // out[i] = worker w's element i of the table pieces at base, i < P (out of
-// any alignment).
+// any alignment).  Bound by memory: a thread copies the four elements of one
+// 16-byte aligned chunk of out, `lead` being the elements out lies past such an
+// address (0 to 3), from a source that need only be 4-byte aligned; chunks
+// that reach over out's ends or a tile's edge go element by element.  One
+// element per thread (the form without VEC, kept for an out not even aligned
+// to 4 bytes) moved 25M elements in 57 us, 3.5 TB/s.
+template <bool VEC>
 __global__ __launch_bounds__(kBlock) void read_row_kernel(const float* __restrict__ base,
                                                           int64_t nw, int32_t w, int64_t P,
-                                                          float* __restrict__ out)
+                                                          int32_t lead, float* __restrict__ out)
 {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i < P) out[i] = base[tile_index(nw, w, i)];
+    const int64_t c = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if constexpr (!VEC) {
+        if (c < P) out[c] = base[tile_index(nw, w, c)];
+    } else {
+        const int64_t i = 4 * c - lead;
+        if (i >= 0 && i + 4 <= P && (i & (kTileElems - 1)) <= kTileElems - 4) {
+            float4 v;
+            __builtin_memcpy(&v, base + tile_index(nw, w, i), sizeof(v));
+            *reinterpret_cast<float4*>(out + i) = v;
+        } else {
+            for (int64_t k = i < 0 ? 0 : i; k < i + 4 && k < P; ++k) out[k] = base[tile_index(nw, w, k)];
+        }
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void gather_kernel(const float* __restrict__ src,
@@ -1666,8 +1683,15 @@ hipError_t launch_read_row(const float* base, int64_t nw, int32_t w, int64_t P, 
                            hipStream_t stream)
 {
     if (P <= 0) return hipSuccess;
-    hipLaunchKernelGGL(read_row_kernel, dim3(blocks_for(P)), dim3(kBlock), 0, stream, base, nw, w,
-                       P, out);
+    const auto at = reinterpret_cast<uintptr_t>(out);
+    if (at % 4 != 0) {
+        hipLaunchKernelGGL(read_row_kernel<false>, dim3(blocks_for(P)), dim3(kBlock), 0, stream, base,
+                           nw, w, P, 0, out);
+    } else {
+        const int32_t lead = static_cast<int32_t>(at / 4 % 4);
+        hipLaunchKernelGGL(read_row_kernel<true>, dim3(blocks_for((P + lead + 3) / 4)), dim3(kBlock), 0,
+                           stream, base, nw, w, P, lead, out);
+    }
     return hipGetLastError();
 }
 

@@ -111,3 +111,22 @@ def test_literal_pi_with_nan(G):
     P, n, T = 1030, 6, 400
     hp = _hp(G, pi_mode=G.GEM_PI_LITERAL)
     _case(G, P, n, T, 8, hp, chunks=(0, 8))
+
+
+@pytest.mark.parametrize("P", [1, 3, 4, 5, 8191, 8192, 8195, 24_581])
+def test_read_state_into_any_alignment(G, P):
+    """Rows read to device addresses 0 to 3 elements past a 16-byte boundary,
+    and one byte off: the same elements, and nothing beside them."""
+    import torch
+    n = 3
+    theta = np.random.default_rng(P).standard_normal(P).astype(np.float32)
+    with G.Gem(P, n) as g:
+        G.gem_set_theta(g.h, theta)
+        raw = torch.zeros(4 * P + 64, dtype=torch.uint8, device="cuda")
+        for off in (0, 4, 8, 12, 1):
+            raw.fill_(0xAB)
+            rc = G.lib().gem_read_state(g.h, 2, G.GEM_SNAPSHOT, raw.data_ptr() + 16 + off, 1)
+            assert rc == G.GEM_OK
+            got = raw.cpu().numpy()
+            assert np.array_equal(got[16 + off:16 + off + 4 * P], theta.view(np.uint8)), off
+            assert (got[:16 + off] == 0xAB).all() and (got[16 + off + 4 * P:] == 0xAB).all(), off

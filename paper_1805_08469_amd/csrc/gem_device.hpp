@@ -56,6 +56,46 @@ __host__ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, ui
     return Words4{c0, c1, c2, c3};
 }
 
+// The same for the noise's counters (q_lo, q_hi, t, 0), whose q_hi and keys are
+// uniform.  What a commit loop's compiler can keep or compute once is grouped
+// so that it does: the first round's product with q_lo does not depend on t,
+// nor does the second round's with word 2; with a uniform t (UNIFORM) the
+// other two products of these rounds and their XORs are scalar.  The rest is
+// two products and two XORs a round from the third on: 34 vector instructions
+// a commit, 42 before they were grouped.
+template <bool UNIFORM>
+__device__ __forceinline__ Words4 philox10_noise(uint32_t q_lo, uint32_t q_hi, uint32_t t,
+                                                 uint32_t k0, uint32_t k1)
+{
+    constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u, kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;
+    uint64_t pa = static_cast<uint64_t>(kM0) * q_lo;
+    uint64_t pb = static_cast<uint64_t>(kM1) * t;
+    uint32_t c0 = static_cast<uint32_t>(pb >> 32) ^ (q_hi ^ k0);
+    uint32_t c2 = static_cast<uint32_t>(pa >> 32) ^ k1;
+    uint32_t c1 = static_cast<uint32_t>(pb), c3 = static_cast<uint32_t>(pa);
+    k0 += kW0;
+    k1 += kW1;
+    pa = static_cast<uint64_t>(kM0) * c0;
+    pb = static_cast<uint64_t>(kM1) * c2;
+    c0 = c1 ^ (static_cast<uint32_t>(pb >> 32) ^ k0);
+    c2 = static_cast<uint32_t>(pa >> 32) ^ (c3 ^ k1);
+    c1 = static_cast<uint32_t>(pb);
+    c3 = static_cast<uint32_t>(pa);
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        k0 += kW0;
+        k1 += kW1;
+        pa = static_cast<uint64_t>(kM0) * c0;
+        pb = static_cast<uint64_t>(kM1) * c2;
+        c0 = xor3(static_cast<uint32_t>(pb >> 32), c1, k0);
+        c2 = UNIFORM && r == 2 ? static_cast<uint32_t>(pa >> 32) ^ (c3 ^ k1)
+                               : xor3(static_cast<uint32_t>(pa >> 32), c3, k1);
+        c1 = static_cast<uint32_t>(pb);
+        c3 = static_cast<uint32_t>(pa);
+    }
+    return Words4{c0, c1, c2, c3};
+}
+
 // ---------------------------------------------------------------------------
 // Correctly rounded division and square root for operand ranges where the
 // general IEEE sequences' range handling has nothing to do.  hipcc lowers a / b
@@ -68,18 +108,24 @@ __host__ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, ui
 // ---------------------------------------------------------------------------
 
 // a / b, correctly rounded, for normal b and a quotient well inside the
-// normal range (no scaling of either operand).
+// normal range (no scaling of either operand).  The reciprocal takes one Newton
+// step, the quotient one residual correction: correctly rounded for all 2^46
+// pairs of significands (the self-test library checks each on the device; the
+// steps commute with scaling by powers of two in this range).  Correcting with
+// the unrefined reciprocal fails on 26473 of those pairs.
 __device__ __forceinline__ float div_rn_core(float a, float b)
 {
     float r = __builtin_amdgcn_rcpf(b);
     const float e = __builtin_fmaf(-b, r, 1.0f);
     r = __builtin_fmaf(e, r, r);                    // refined reciprocal
-    float q = a * r;
+    const float q = a * r;
     const float e2 = __builtin_fmaf(-b, q, a);
-    q = __builtin_fmaf(e2, r, q);
-    const float e3 = __builtin_fmaf(-b, q, a);
-    return __builtin_fmaf(e3, r, q);
+    return __builtin_fmaf(e2, r, q);
 }
+
+// The product by the rule that zero times anything is zero (V_MUL_LEGACY_F32;
+// the compiler has the intrinsic but no builtin for it).
+__device__ float mul_legacy(float a, float b) __asm("llvm.amdgcn.fmul.legacy");
 
 // sqrt(x), correctly rounded, for the Box-Muller radicands x = -2 ln(k 2^-24),
 // k in [1, 2^24] (+0 or in [1.1e-7, 33.3]).  One Newton step from the hardware
@@ -87,12 +133,13 @@ __device__ __forceinline__ float div_rn_core(float a, float b)
 // correctly rounded root for every one of the 2^24 radicands (the self-test
 // library checks all of them on the device).  Five instructions and the root;
 // stepping v_sqrt's result to the neighbour with the right residual sign takes
-// eight.  x = 0 takes y = 2^50, so g = 0 and the correction is 0; y / 2 is an
-// integer step of the exponent.
+// eight.  x = 0 has y = inf; the legacy product, whose zero times anything is
+// zero, makes g = 0 and the correction 0 * 2^127.  y / 2 is an integer step of
+// the exponent.
 __device__ __forceinline__ float radicand_root(float x)
 {
-    const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(x, 0x1p-100f));
-    const float g = x * y;
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float g = mul_legacy(x, y);
     const float half_y = __uint_as_float(__float_as_uint(y) - 0x00800000u);
     const float e = __builtin_fmaf(-g, g, x);
     return __builtin_fmaf(e, half_y, g);
@@ -145,16 +192,19 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 //
 // The reduction works on the integer: k as binary32 (exact) has u's
 // significand and an exponent 24 larger; subtracting the bits of 2^24 * the
-// least binary32 above sqrt(1/2) leaves e in the bits above the significand
-// and f's significand offset below them.
+// least binary32 above sqrt(1/2) leaves e in the bits above the significand.
+// Those bits alone, as an integer, are e 2^23 (the constants of e carry 2^-23),
+// and k's bits less them are 2^24 f: the quotient of 2^24 (f - 1) and
+// 2^24 (f + 1) is the same.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float radicand_of_k24(uint32_t k)
 {
     constexpr uint32_t kLeast = 0x3F3504F4u;   // least binary32 above sqrt(1/2)
-    const uint32_t ix = __float_as_uint(static_cast<float>(k)) - (kLeast + (24u << 23));
-    const float ef = static_cast<float>(static_cast<int32_t>(ix) >> 23);
-    const float f = __uint_as_float((ix & 0x007FFFFFu) + kLeast);
-    const float s = ln_quotient(__builtin_fmaf(f, -4.0f, 4.0f), f + 1.0f);   // -4 (f-1)/(f+1)
+    const uint32_t bits = __float_as_uint(static_cast<float>(k));
+    const uint32_t eb = (bits - (kLeast + (24u << 23))) & 0xFF800000u;
+    const float ef = static_cast<float>(static_cast<int32_t>(eb));          // 2^23 e
+    const float f = __uint_as_float(bits - eb);                             // 2^24 f
+    const float s = ln_quotient(__builtin_fmaf(f, -4.0f, 0x1p26f), f + 0x1p24f);   // -4 (f-1)/(f+1)
     const float z = s * s;
     float p = (1.0f / 9.0f) * 0x1p-16f;
     p = __builtin_fmaf(p, z, (1.0f / 7.0f) * 0x1p-12f);
@@ -164,8 +214,8 @@ __device__ __forceinline__ float radicand_of_k24(uint32_t k)
     const float ln_f = __builtin_fmaf(s, p, s);   // -2 ln f
     const float ln2_tail = 0x1.7f7d1cp-20f;       // RN(ln 2 - ln2_head)
     const float ln2_head = 0x1.62e4p-1f;
-    const float r = __builtin_fmaf(ef, -2.0f * ln2_tail, ln_f);
-    return __builtin_fmaf(ef, -2.0f * ln2_head, r);
+    const float r = __builtin_fmaf(ef, -2.0f * ln2_tail * 0x1p-23f, ln_f);
+    return __builtin_fmaf(ef, -2.0f * ln2_head * 0x1p-23f, r);
 }
 
 // r cos(phi) and r sin(phi) for phi = 2 pi (xb >> 8) / 2^24.  With k = xb >> 8,
@@ -199,10 +249,12 @@ __device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, floa
     pc = __builtin_fmaf(pc, x2, -0.5f);
     const float cx = __builtin_fmaf(pc, x2, 1.0f);
 
-    const bool odd = static_cast<int32_t>((xb << 1) + 0x40000000u) < 0;   // bit 30 of xb + 2^29
-    // r ^ ((xb + 2^29) & sign bit): one V_BITOP3_B32 (a ^ (b & c), table 0x78)
+    // bit 30 of y = xb + 2^29: |y| as a binary32 is at least 2 (or a NaN) with it
+    const uint32_t y = xb + 0x20000000u;
+    const bool odd = !(__builtin_fabsf(__uint_as_float(y)) < 2.0f);
+    // r ^ (y & sign bit): one V_BITOP3_B32 (a ^ (b & c), table 0x78)
     const float rs = __uint_as_float(__builtin_amdgcn_bitop3_b32(
-        __float_as_uint(r), xb + 0x20000000u, 0x80000000u, 0x78));
+        __float_as_uint(r), y, 0x80000000u, 0x78));
     zs = rs * (odd ? cx : sx);
     zc = rs * (odd ? -sx : cx);
 }
@@ -214,27 +266,36 @@ __device__ __forceinline__ void box_muller(uint32_t xa, uint32_t xb, float& zc, 
     turn_times(radicand_root(radicand_of_k24((xa >> 8) + 1u)), xb, zc, zs);
 }
 
-// Four standard normals for elements 4q..4q+3 at clock t.
+// Four standard normals for elements 4q..4q+3 at clock t.  UNIFORM: t is the
+// same for the whole wave.
+template <bool UNIFORM = true>
 __device__ __forceinline__ float4 normals4(uint64_t q, uint32_t t, uint32_t k0, uint32_t k1)
 {
-    const Words4 w = philox10(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), t, 0u,
-                              k0, k1);
+    const Words4 w = philox10_noise<UNIFORM>(static_cast<uint32_t>(q),
+                                             static_cast<uint32_t>(q >> 32), t, k0, k1);
     float4 z;
     box_muller(w.x0, w.x1, z.x, z.y);
     box_muller(w.x2, w.x3, z.z, z.w);
     return z;
 }
 
-// binary32 -> bfloat16 -> binary32, nearest-even; NaN stays a (quiet) NaN.
-__device__ __forceinline__ float round_to_bf16(float x)
+// Two binary32 values rounded to bfloat16, nearest-even (a NaN stays a quiet
+// NaN), packed low half first: one V_CVT_PK_BF16_F32.  The integer steps of the
+// rounding take 7 instructions for each value; the self-test library checks
+// all 2^32 inputs against them.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    uint32_t b = __float_as_uint(x);
-    if ((b & 0x7FFFFFFFu) > 0x7F800000u) {
-        b = (b | 0x00400000u) & 0xFFFF0000u;
-    } else {
-        b = (b + 0x7FFFu + ((b >> 16) & 1u)) & 0xFFFF0000u;
-    }
-    return __uint_as_float(b);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Both values rounded to bfloat16, as binary32.
+__device__ __forceinline__ void round_pair_to_bf16(float& a, float& b)
+{
+    const uint32_t p = pack_bf16(a, b);
+    a = __uint_as_float(p << 16);
+    b = __uint_as_float(p & 0xFFFF0000u);
 }
 
 }  // namespace gemk

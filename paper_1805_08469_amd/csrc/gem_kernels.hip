@@ -217,16 +217,35 @@ __device__ __forceinline__ void commit_element(const PassArgs& a, int tau, float
     m = mn;
 }
 
-// The simulated worker's update at snapshot s (notation table: -eta grad L(s)).
-template <bool BF16>
-__device__ __forceinline__ float stale_update(float neg_lr, float sigma, float s, float h, float ts,
-                                              float z)
+// The simulated worker's updates at W snapshot elements (notation table:
+// -eta grad L(s)).
+template <int W, bool BF16>
+__device__ __forceinline__ void stale_updates(float neg_lr, float sigma, const float* s,
+                                              const float* h, const float* ts, const float* z,
+                                              float* d)
 {
-    const float nz = sigma * z;
-    const float g = __builtin_fmaf(h, s - ts, nz);
-    float d = neg_lr * g;
-    if (BF16) d = round_to_bf16(d);
-    return d;
+    static_assert(W % 2 == 0, "pairs are rounded together");
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const float nz = sigma * z[k];
+        const float g = __builtin_fmaf(h[k], s[k] - ts[k], nz);
+        d[k] = neg_lr * g;
+    }
+    if constexpr (BF16) {
+#pragma unroll
+        for (int k = 0; k < W; k += 2) round_pair_to_bf16(d[k], d[k + 1]);
+    }
+}
+
+template <bool BF16>
+__device__ __forceinline__ float4 stale_update4(float neg_lr, float sigma, const float4& s,
+                                                const float4& h, const float4& ts, const float4& z)
+{
+    const float sv[4] = {s.x, s.y, s.z, s.w}, hv[4] = {h.x, h.y, h.z, h.w};
+    const float tv[4] = {ts.x, ts.y, ts.z, ts.w}, zv[4] = {z.x, z.y, z.z, z.w};
+    float d[4];
+    stale_updates<4, BF16>(neg_lr, sigma, sv, hv, tv, zv, d);
+    return make_float4(d[0], d[1], d[2], d[3]);
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b16) { return __uint_as_float(b16 << 16); }
@@ -439,10 +458,7 @@ __device__ __forceinline__ StepOut pass_step(const PassArgs& a, int j, Chunk& ch
         const uint64_t q = (static_cast<uint64_t>(ch.q_hi) << 32) | ch.q_lo;
         const float4 z = normals4(q, a.t0 + static_cast<uint32_t>(j),
                                   a.key0, a.key1);
-        d.x = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.x, ch.hh.x, ch.tt.x, z.x);
-        d.y = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.y, ch.hh.y, ch.tt.y, z.y);
-        d.z = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.z, ch.hh.z, ch.tt.z, z.z);
-        d.w = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.w, ch.hh.w, ch.tt.w, z.w);
+        d = stale_update4<BF16>(a.neg_lr, a.sigma, rows.s, ch.hh, ch.tt, z);
     } else {
         d = ch.active ? load_given<SRC>(a.upd[j], ch.c, a.P) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -894,10 +910,7 @@ __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
         }
         float4 m = global_m ? mg : rows.m;
         float4 d;
-        d.x = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.x, hh.x, tt.x, z.x);
-        d.y = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.y, hh.y, tt.y, z.y);
-        d.z = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.z, hh.z, tt.z, z.z);
-        d.w = stale_update<BF16>(a.neg_lr, a.sigma, rows.s.w, hh.w, tt.w, z.w);
+        d = stale_update4<BF16>(a.neg_lr, a.sigma, rows.s, hh, tt, z);
         z = noise(j + 1);
         float4 snap;
         if constexpr (V == Variant::General) {
@@ -1062,10 +1075,7 @@ void seg_step_kernel(const SegArgs a)
         float4 d;
         if (SRC == Source::Generated) {
             const float4 z = normals4(static_cast<uint64_t>(c), a.t - 1u, a.key0, a.key1);
-            d.x = stale_update<BF16>(a.neg_lr, a.sigma, sp.x, hv.x, tv.x, z.x);
-            d.y = stale_update<BF16>(a.neg_lr, a.sigma, sp.y, hv.y, tv.y, z.y);
-            d.z = stale_update<BF16>(a.neg_lr, a.sigma, sp.z, hv.z, tv.z, z.z);
-            d.w = stale_update<BF16>(a.neg_lr, a.sigma, sp.w, hv.w, tv.w, z.w);
+            d = stale_update4<BF16>(a.neg_lr, a.sigma, sp, hv, tv, z);
         } else {
             d = load_given<SRC>(a.upd_prev, c, a.P);
         }
@@ -1125,10 +1135,7 @@ void seg_step_kernel(const SegArgs a)
         else s = s_cur;
         if (SRC == Source::Generated) {
             const float4 z = normals4(static_cast<uint64_t>(c), a.t, a.key0, a.key1);
-            d.x = stale_update<BF16>(a.neg_lr, a.sigma, s.x, hv.x, tv.x, z.x);
-            d.y = stale_update<BF16>(a.neg_lr, a.sigma, s.y, hv.y, tv.y, z.y);
-            d.z = stale_update<BF16>(a.neg_lr, a.sigma, s.z, hv.z, tv.z, z.z);
-            d.w = stale_update<BF16>(a.neg_lr, a.sigma, s.w, hv.w, tv.w, z.w);
+            d = stale_update4<BF16>(a.neg_lr, a.sigma, s, hv, tv, z);
         } else {
             d = load_given<SRC>(a.upd_cur, c, a.P);
         }
@@ -1337,11 +1344,8 @@ __global__ __launch_bounds__(kBlock) void generate_kernel(const float* __restric
     const float4 hv = *reinterpret_cast<const float4*>(h + i0);
     const float4 tv = *reinterpret_cast<const float4*>(ts + i0);
     const float4 z = normals4(static_cast<uint64_t>(c), t, key0, key1);
-    float d[4];
-    d[0] = stale_update<BF16>(neg_lr, sigma, s.x, hv.x, tv.x, z.x);
-    d[1] = stale_update<BF16>(neg_lr, sigma, s.y, hv.y, tv.y, z.y);
-    d[2] = stale_update<BF16>(neg_lr, sigma, s.z, hv.z, tv.z, z.z);
-    d[3] = stale_update<BF16>(neg_lr, sigma, s.w, hv.w, tv.w, z.w);
+    const float4 u4 = stale_update4<BF16>(neg_lr, sigma, s, hv, tv, z);
+    const float d[4] = {u4.x, u4.y, u4.z, u4.w};
     if (BF16) {
         uint16_t* o = static_cast<uint16_t*>(out);
         if (i0 + 4 <= P) {

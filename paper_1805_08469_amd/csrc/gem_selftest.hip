@@ -12,6 +12,9 @@
 //     against the IEEE square root;
 //   - r cos(phi), r sin(phi) for all 2^24 angles and both signs of r against
 //     the defined steps of sin and cos;
+//   - the core quotient div_rn_core on every pair of significands;
+//   - the rounding to bfloat16 of every binary32 value, and the noise's Philox
+//     words against the generator's plain rounds;
 //   - the guarded quotient div_rn on Philox-random operand pairs spread over
 //     the whole binary32 range (zeros, subnormals, infinities and NaNs
 //     included), and on every significand of the denominator against a set
@@ -161,6 +164,64 @@ __global__ __launch_bounds__(kThreads) void div_grid_kernel(const float* nums, i
     if (miss) atomicAdd(bad, static_cast<unsigned long long>(miss));
 }
 
+// div_rn_core of every pair of numerator significand a0 + r, r < count, and
+// denominator significand (a thread each): the residual num - den q is exact, and
+// q is the correctly rounded quotient iff it lies within half a unit of q's last
+// place times den (2^-24 den for q in [1, 2), 2^-25 den below 1; ties do not occur).
+__global__ __launch_bounds__(kThreads) void div_core_kernel(uint32_t a0, uint32_t count,
+                                                            unsigned long long* bad)
+{
+    const uint32_t m = blockIdx.x * kThreads + threadIdx.x;   // grid covers 2^23 exactly
+    const float den = __uint_as_float(0x3F800000u | m);
+    uint32_t miss = 0;
+    for (uint32_t r = 0; r < count; ++r) {
+        const float num = __uint_as_float(0x3F800000u | (a0 + r));
+        const float half = (a0 + r >= m ? 0x1p-24f : 0x1p-25f) * den;
+        const float res = __builtin_fmaf(-den, gemk::div_rn_core(num, den), num);
+        miss += __builtin_fabsf(res) < half ? 0u : 1u;
+    }
+    if (miss) atomicAdd(bad, static_cast<unsigned long long>(miss));
+}
+
+// binary32 -> bfloat16 -> binary32, nearest-even; NaN stays a (quiet) NaN: the
+// defined steps, on the integer.
+__device__ float defined_bf16(float x)
+{
+    uint32_t b = __float_as_uint(x);
+    if ((b & 0x7FFFFFFFu) > 0x7F800000u) b = (b | 0x00400000u) & 0xFFFF0000u;
+    else b = (b + 0x7FFFu + ((b >> 16) & 1u)) & 0xFFFF0000u;
+    return __uint_as_float(b);
+}
+
+__global__ __launch_bounds__(kThreads) void bf16_kernel(unsigned long long* bad)
+{
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;   // grid covers 2^24 exactly
+    uint32_t miss = 0;
+    for (uint32_t hi = 0; hi < 256; ++hi) {
+        const float x = __uint_as_float((hi << 24) | i), y = __uint_as_float(((hi << 24) | i) * 2654435761u);
+        float a = x, b = y;
+        gemk::round_pair_to_bf16(a, b);
+        miss += __float_as_uint(a) != __float_as_uint(defined_bf16(x));
+        miss += __float_as_uint(b) != __float_as_uint(defined_bf16(y));
+    }
+    if (miss) atomicAdd(bad, static_cast<unsigned long long>(miss));
+}
+
+// The noise's words of counters (i, q_hi, t, 0), t uniform and per lane.
+__global__ __launch_bounds__(kThreads) void noise_words_kernel(uint32_t q_hi, uint32_t t, uint32_t k0,
+                                                               uint32_t k1, unsigned long long* bad)
+{
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t tl = t + (threadIdx.x & 1u);
+    const gemk::Words4 a = gemk::philox10(i, q_hi, t, 0u, k0, k1);
+    const gemk::Words4 b = gemk::philox10_noise<true>(i, q_hi, t, k0, k1);
+    const gemk::Words4 c = gemk::philox10(i, q_hi, tl, 0u, k0, k1);
+    const gemk::Words4 d = gemk::philox10_noise<false>(i, q_hi, tl, k0, k1);
+    const bool ok = a.x0 == b.x0 && a.x1 == b.x1 && a.x2 == b.x2 && a.x3 == b.x3 &&
+                    c.x0 == d.x0 && c.x1 == d.x1 && c.x2 == d.x2 && c.x3 == d.x3;
+    if (!ok) atomicAdd(bad, 1ull);
+}
+
 template <typename Launch>
 int run_counting(Launch launch, uint64_t* mismatches)
 {
@@ -205,6 +266,38 @@ int gem_selftest_turn(float r, uint64_t* mismatches)
     if (!mismatches) return GEM_EINVAL;
     return run_counting([&](unsigned long long* bad) {
         hipLaunchKernelGGL(turn_kernel, dim3((1u << 24) / kThreads), dim3(kThreads), 0, 0, r, bad);
+    }, mismatches);
+}
+
+// Numerator significands [a0, a0 + count), a0 + count <= 2^23, against all denominators'.
+int gem_selftest_div_core(uint32_t a0, uint32_t count, uint64_t* mismatches)
+{
+    if (!mismatches || count > (1u << 23) || a0 > (1u << 23) - count) return GEM_EINVAL;
+    return run_counting([&](unsigned long long* bad) {
+        // launches of a fraction of a second each
+        for (uint32_t done = 0; done < count;) {
+            const uint32_t part = count - done < (1u << 14) ? count - done : 1u << 14;
+            hipLaunchKernelGGL(div_core_kernel, dim3((1u << 23) / kThreads), dim3(kThreads), 0, 0,
+                               a0 + done, part, bad);
+            done += part;
+        }
+    }, mismatches);
+}
+
+int gem_selftest_bf16(uint64_t* mismatches)
+{
+    if (!mismatches) return GEM_EINVAL;
+    return run_counting([](unsigned long long* bad) {
+        hipLaunchKernelGGL(bf16_kernel, dim3((1u << 24) / kThreads), dim3(kThreads), 0, 0, bad);
+    }, mismatches);
+}
+
+int gem_selftest_noise_words(uint32_t q_hi, uint32_t t, uint64_t seed, uint64_t* mismatches)
+{
+    if (!mismatches) return GEM_EINVAL;
+    return run_counting([&](unsigned long long* bad) {
+        hipLaunchKernelGGL(noise_words_kernel, dim3(1u << 12), dim3(kThreads), 0, 0, q_hi, t,
+                           static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), bad);
     }, mismatches);
 }
 

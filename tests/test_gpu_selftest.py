@@ -32,6 +32,9 @@ def lib():
     L.gem_selftest_ln_div.argtypes = [u64p]
     L.gem_selftest_radius.argtypes = [u64p]
     L.gem_selftest_turn.argtypes = [C.c_float, u64p]
+    L.gem_selftest_div_core.argtypes = [C.c_uint32, C.c_uint32, u64p]
+    L.gem_selftest_bf16.argtypes = [u64p]
+    L.gem_selftest_noise_words.argtypes = [C.c_uint32, C.c_uint32, C.c_uint64, u64p]
     L.gem_selftest_div_random.argtypes = [C.c_uint64, C.c_int64, u64p]
     L.gem_selftest_div_grid.argtypes = [C.POINTER(C.c_float), C.c_int32, C.c_int32, u64p]
     return L
@@ -56,6 +59,22 @@ def test_box_muller_radius_exhaustive(lib):
 def test_angle_products_exhaustive(lib, r):
     """r cos(phi) and r sin(phi) of every angle against the defined steps."""
     assert _count(lib.gem_selftest_turn, r) == 0
+
+
+@pytest.mark.parametrize("part", range(8))
+def test_core_quotient_exhaustive(lib, part):
+    """All 2^46 pairs of significands, an eighth of the numerators at a time."""
+    assert _count(lib.gem_selftest_div_core, part << 20, 1 << 20) == 0
+
+
+def test_bf16_rounding_exhaustive(lib):
+    assert _count(lib.gem_selftest_bf16) == 0
+
+
+@pytest.mark.parametrize("q_hi,t,seed", [(0, 0, 0), (0, 2 ** 32 - 2, 2 ** 64 - 1),
+                                         (3, 123456789, 0x9E3779B97F4A7C15)])
+def test_noise_words(lib, q_hi, t, seed):
+    assert _count(lib.gem_selftest_noise_words, q_hi, t, seed) == 0
 
 
 @pytest.mark.parametrize("seed", [1, 20180522])

@@ -348,6 +348,23 @@ RunShape run_shape(const gem_handle* g, gemk::Variant v, int64_t k, int64_t dist
     return r;
 }
 
+// Whether a launch of k commits by `distinct` workers goes to the short-vector
+// kernel, which holds all their rows in LDS.  It takes 0.12 us a commit for as
+// many blocks as are resident, up to 8 a compute unit with 20 workers and 2 with
+// 100; run_kernel takes 0.5 up to 262144 elements.  Past twice the resident blocks
+// or 8 a compute unit the latter's fewer instructions per element win.  Measured
+// (400 commits and the reads after them, short and run kernel, us): 20 workers,
+// 65536 elements 199 and 342, 131072: 257 and 345, 262144: 341 and 351, 524288:
+// 522 and 438; 100 workers, 32768: 192 and 343, 65536: 261 and 343, 131072: 386 and
+// 347; kappa = 2, 131072: 322 and 421, 262144: 440 and 423.
+bool short_run(const gem_handle* g, int64_t distinct, int k, bool adaptive)
+{
+    if (distinct > gemk::kShortSlots) return false;
+    const int64_t lds = gemk::short_run_lds(static_cast<int>(distinct), k, adaptive);
+    const int64_t per_cu = (g->Pp / gemk::kShortElems + g->cus - 1) / g->cus;
+    return per_cu <= std::min<int64_t>(8, 2 * (g->lds_per_cu / lds));
+}
+
 // Queue a run of T commits on generated updates as launches of up to
 // kRunCommits commits each; advance the clock and pull bookkeeping.  The work
 // counters count the passes of at most K commits that run_passes would launch.
@@ -396,16 +413,20 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
         }
         for (int j = 0; j < k; ++j) last[w[j]] = -1;
         const RunShape shape = run_shape(g, variant, k, distinct);
-        gemk::plan_run(w, k, gemk::kRunDepth, shape.slots, a.sched, last.data());
+        const bool is_short = short_run(g, distinct, k, adaptive);
+        if (is_short) gemk::plan_short_run(w, k, a.sched, last.data());
+        else gemk::plan_run(w, k, gemk::kRunDepth, shape.slots, a.sched, last.data());
         a.t0 = static_cast<uint32_t>(g->t);
         a.K = k;
         for (int j = 0; adaptive && j < k; ++j) {
             a.sched[gemk::kRunTauAt + j] = static_cast<uint32_t>(g->t + j - pull[w[j]]);
             pull[w[j]] = next_pull(g, g->t + j);
         }
-        GEM_HIP(gemk::launch_run(a, variant, g->sp.update_dtype == GEM_BF16, shape.stream,
-                                 static_cast<uint32_t>(shape.slots * gemk::run_slot_bytes(variant)),
-                                 g->stream));
+        const bool bf16 = g->sp.update_dtype == GEM_BF16;
+        if (is_short) GEM_HIP(gemk::launch_short_run(a, variant, bf16, g->stream));
+        else GEM_HIP(gemk::launch_run(a, variant, bf16, shape.stream,
+                                      static_cast<uint32_t>(shape.slots * gemk::run_slot_bytes(variant)),
+                                      g->stream));
         for (int j = 0; j < k; ++j) {
             g->pc[w[j]] = next_pull(g, g->t + j);
             if ((j0 + j) % K == 0) {

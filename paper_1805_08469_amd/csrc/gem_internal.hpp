@@ -166,10 +166,11 @@ constexpr int run_slot_bytes(Variant v) { return v == Variant::FastGlobal ? 4096
 // run_slot_bytes(v) each.  Fast and FastGlobal need eps >= 2^-60.
 hipError_t launch_run(const RunArgs& a, Variant v, bool bf16_out, bool stream_rows,
                       uint32_t lds_bytes, hipStream_t stream);
+// The same over a short vector (short_run_kernel), a.sched packed by plan_short_run.
+hipError_t launch_short_run(const RunArgs& a, Variant v, bool bf16_out, hipStream_t stream);
 hipError_t launch_pass(const PassArgs& a, Source src, Variant v, bool bf16_out, bool diag,
                        bool rec, int depth, bool stream_rows, uint32_t deep_lds,
                        hipStream_t stream);
-
 
 // Infinity Cache of one MI355X: a state this small stays cached across passes.
 constexpr int64_t kInfinityCacheBytes = int64_t{256} << 20;

@@ -91,9 +91,32 @@ __device__ __forceinline__ int scale_bin(float x)
 // instructions more).
 __device__ __forceinline__ void keep(float& x) { asm volatile("" : "+v"(x)); }
 
-// The default rule's step on a thread's four elements (Fast variants, no
+// The least |num|, and the greatest |num| or den, of W quotients.  (Written as
+// chains that the three-operand minimum and maximum instructions take.)
+template <int W>
+__device__ __forceinline__ void magnitudes(const float (&num)[W], const float (&den)[W], float& lo,
+                                           float& hi)
+{
+    if constexpr (W == 1) {
+        lo = __builtin_fabsf(num[0]);
+        hi = __builtin_fmaxf(lo, den[0]);
+        return;
+    } else {
+        hi = __builtin_fmaxf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+        lo = __builtin_fminf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
+#pragma unroll
+        for (int k = 2; k < W; k += 2) {
+            hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(num[k])), __builtin_fabsf(num[k + 1]));
+            lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[k])), __builtin_fabsf(num[k + 1]));
+        }
+#pragma unroll
+        for (int k = 0; k < W; k += 2) hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[k]), den[k + 1]);
+    }
+}
+
+// The default rule's step on a thread's W elements (Fast variants, no
 // diagnostics): the same arithmetic as commit_element, with one range check
-// for the four quotients.  When all eight operand magnitudes lie in
+// for the W quotients.  When all the operand magnitudes lie in
 // [2^-60, 2^60], each quotient is div_rn_core -- what div_rn takes for each of
 // them; otherwise each goes through div_rn.  A denominator |d| + eps is at
 // least eps, so with eps >= 2^-60 (the default is 1e-16) only the numerators
@@ -102,56 +125,57 @@ __device__ __forceinline__ void keep(float& x) { asm volatile("" : "+v"(x)); }
 // clamp makes either pi = 0.
 // SMALL_EPS: eps may be below 2^-60 (else the caller has made sure it is not,
 // and the step is one straight run of instructions but for the rare fallback).
-template <bool SMALL_EPS, typename Args>
-__device__ __forceinline__ void commit4_fast(const Args& a, const float4& d, const float4& s,
-                                             float4& th, float4& m, float4& snap,
-                                             float* pi_out = nullptr)
+template <int W, bool SMALL_EPS, typename Args>
+__device__ __forceinline__ void commit_fast(const Args& a, const float (&d)[W], const float (&s)[W],
+                                            float (&th)[W], float (&m)[W], float* pi_out = nullptr)
 {
-    const float dv[4] = {d.x, d.y, d.z, d.w};
-    const float sv[4] = {s.x, s.y, s.z, s.w};
-    float tv[4] = {th.x, th.y, th.z, th.w};
-    float mv[4] = {m.x, m.y, m.z, m.w};
-    float num[4], den[4];
+    float num[W], den[W];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        mv[k] = __builtin_fmaf(a.mu, mv[k], dv[k]);                 // Alg. 1: m <- mu m + dtheta
-        const float drift = tv[k] - sv[k];                          // theta_t - s_t (eq. 16)
-        num[k] = __builtin_fabsf(mv[k]) - __builtin_fabsf(drift);
-        den[k] = __builtin_fabsf(dv[k]) + a.eps;
+    for (int k = 0; k < W; ++k) {
+        m[k] = __builtin_fmaf(a.mu, m[k], d[k]);                    // Alg. 1: m <- mu m + dtheta
+        const float drift = th[k] - s[k];                           // theta_t - s_t (eq. 16)
+        num[k] = __builtin_fabsf(m[k]) - __builtin_fabsf(drift);
+        den[k] = __builtin_fabsf(d[k]) + a.eps;
     }
-    float hi = __builtin_fmaxf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
-    float lo = __builtin_fminf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
-    hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
-    lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
-    hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[0]), den[1]);
-    hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[2]), den[3]);
+    float lo, hi;
+    magnitudes(num, den, lo, hi);
     if constexpr (SMALL_EPS) {
         keep(hi);
         // (on eps's bits: a scalar comparison; eps is positive)
         if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
-            lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
-            lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
+#pragma unroll
+            for (int k = 0; k < W; ++k) lo = __builtin_fminf(lo, den[k]);
         }
     }
     // eq. 18, clamped at +0 (pi = q > 0 ? q : +0).  The median of q, 0 and inf
     // is the clamp in one instruction, a NaN's being 0 (the median instruction
     // takes the minimum of the other two).
-    float pi[4];
+    float pi[W];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < W; ++k)
         pi[k] = __builtin_amdgcn_fmed3f(div_rn_core(num[k], den[k]), 0.0f, __builtin_inff());
     if (__builtin_expect(__ballot(!(lo >= 0x1p-60f && hi <= 0x1p60f)) != 0, 0)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < W; ++k) {
             const float q = div_rn(num[k], den[k]);
             pi[k] = (q > 0.0f) ? q : 0.0f;
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        tv[k] = __builtin_fmaf(pi[k], dv[k], tv[k]);                // eq. 3
+    for (int k = 0; k < W; ++k) {
+        th[k] = __builtin_fmaf(pi[k], d[k], th[k]);                 // eq. 3
         if (pi_out) pi_out[k] = pi[k];
     }
+}
+
+template <bool SMALL_EPS, typename Args>
+__device__ __forceinline__ void commit4_fast(const Args& a, const float4& d, const float4& s,
+                                             float4& th, float4& m, float4& snap,
+                                             float* pi_out = nullptr)
+{
+    const float dv[4] = {d.x, d.y, d.z, d.w}, sv[4] = {s.x, s.y, s.z, s.w};
+    float tv[4] = {th.x, th.y, th.z, th.w}, mv[4] = {m.x, m.y, m.z, m.w};
+    commit_fast<4, SMALL_EPS>(a, dv, sv, tv, mv, pi_out);
     th = make_float4(tv[0], tv[1], tv[2], tv[3]);
     snap = th;
     m = make_float4(mv[0], mv[1], mv[2], mv[3]);
@@ -735,70 +759,74 @@ __global__ __launch_bounds__(kBlock) void pass_kernel(const PassArgs a)
     }
 }
 
-// The general rule's step on a thread's four elements (run kernel, General
+// The general rule's step on a thread's W elements (run kernel, General
 // variant): commit_element's arithmetic, every mode a uniform runtime flag,
-// with one range check for the four quotients as in commit4_fast.
-__device__ __forceinline__ void commit4_general(const RunArgs& a, int tau, const float4& d,
-                                                const float4& s, float4& th, float4& m,
-                                                float4& snap)
+// with one range check for the W quotients as in commit_fast.
+template <int W>
+__device__ __forceinline__ void commit_general(const RunArgs& a, int tau, const float (&d)[W],
+                                               const float (&s)[W], float (&th)[W], float (&m)[W],
+                                               float (&snap)[W])
 {
-    const float dv[4] = {d.x, d.y, d.z, d.w};
-    const float sv[4] = {s.x, s.y, s.z, s.w};
-    float tv[4] = {th.x, th.y, th.z, th.w};
-    float mv[4] = {m.x, m.y, m.z, m.w};
-    float add[4];
+    float next[W];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) mv[k] = __builtin_fmaf(a.mu, mv[k], dv[k]);
+    for (int k = 0; k < W; ++k) m[k] = __builtin_fmaf(a.mu, m[k], d[k]);
     if (a.mode & kModeDownpour) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) tv[k] = tv[k] + dv[k];          // eq. 1
+        for (int k = 0; k < W; ++k) next[k] = th[k] + d[k];         // eq. 1
     } else {
         // num / den: the scale factor (eq. 18), or the damped update itself
         const bool adaptive = (a.mode & kModeAdaptive) != 0;
         const float k_eff = (a.mode & kModeKappaMul) ? a.k_eff : 1.0f;
         const float stale = static_cast<float>(tau + 1);
-        float num[4], den[4], q[4];
+        float num[W], den[W], q[W];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float drift = tv[k] - sv[k];
-            num[k] = adaptive ? dv[k] : k_eff * __builtin_fabsf(mv[k]) - __builtin_fabsf(drift);
-            den[k] = adaptive ? stale : __builtin_fabsf(dv[k]) + a.eps;
+        for (int k = 0; k < W; ++k) {
+            const float drift = th[k] - s[k];
+            num[k] = adaptive ? d[k] : k_eff * __builtin_fabsf(m[k]) - __builtin_fabsf(drift);
+            den[k] = adaptive ? stale : __builtin_fabsf(d[k]) + a.eps;
         }
-        float hi = __builtin_fmaxf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
-        float lo = __builtin_fminf(__builtin_fabsf(num[0]), __builtin_fabsf(num[1]));
-        hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
-        lo = __builtin_fminf(__builtin_fminf(lo, __builtin_fabsf(num[2])), __builtin_fabsf(num[3]));
-        hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[0]), den[1]);
-        hi = __builtin_fmaxf(__builtin_fmaxf(hi, den[2]), den[3]);
+        float lo, hi;
+        magnitudes(num, den, lo, hi);
         keep(hi);
         if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
-            lo = __builtin_fminf(__builtin_fminf(lo, den[0]), den[1]);
-            lo = __builtin_fminf(__builtin_fminf(lo, den[2]), den[3]);
+#pragma unroll
+            for (int k = 0; k < W; ++k) lo = __builtin_fminf(lo, den[k]);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = div_rn_core(num[k], den[k]);
+        for (int k = 0; k < W; ++k) q[k] = div_rn_core(num[k], den[k]);
         if (__builtin_expect(__ballot(!(lo >= 0x1p-60f && hi <= 0x1p60f)) != 0, 0)) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = div_rn(num[k], den[k]);
+            for (int k = 0; k < W; ++k) q[k] = div_rn(num[k], den[k]);
         }
         if (adaptive) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) add[k] = tv[k] + q[k];
+            for (int k = 0; k < W; ++k) next[k] = th[k] + q[k];
         } else {
             const bool literal = (a.mode & kModeLiteralPi) != 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < W; ++k) {
                 const float pi = literal ? q[k] : __builtin_amdgcn_fmed3f(q[k], 0.0f,
                                                                           __builtin_inff());
-                add[k] = __builtin_fmaf(pi, dv[k], tv[k]);          // eq. 3
+                next[k] = __builtin_fmaf(pi, d[k], th[k]);          // eq. 3
             }
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) tv[k] = add[k];
     }
-    const float4 before = th;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        snap[k] = (a.mode & kModePrePull) ? th[k] : next[k];
+        th[k] = next[k];
+    }
+}
+
+__device__ __forceinline__ void commit4_general(const RunArgs& a, int tau, const float4& d,
+                                                const float4& s, float4& th, float4& m,
+                                                float4& snap)
+{
+    const float dv[4] = {d.x, d.y, d.z, d.w}, sv[4] = {s.x, s.y, s.z, s.w};
+    float tv[4] = {th.x, th.y, th.z, th.w}, mv[4] = {m.x, m.y, m.z, m.w}, nv[4];
+    commit_general<4>(a, tau, dv, sv, tv, mv, nv);
     th = make_float4(tv[0], tv[1], tv[2], tv[3]);
-    snap = (a.mode & kModePrePull) ? before : th;
+    snap = make_float4(nv[0], nv[1], nv[2], nv[3]);
     m = make_float4(mv[0], mv[1], mv[2], mv[3]);
 }
 
@@ -946,6 +974,124 @@ __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
         if (j + u < a.K) step(j + u, words[u], ring[u]);
     store4_at<false>(a.theta + blk0, t16, th);
     if (global_m) store4_at<false>(row0 + kTileElems, t16, mg);
+}
+
+// A run over a vector too short to fill the chip with run_kernel's waves.  There a
+// commit takes a wave's 200 instructions one after the other, 0.63 us, however
+// few blocks there are; its serial part is only the step itself.  Here a block has
+// 64 elements, one a lane of one wave (the consumer), every committing worker's
+// pair of rows in LDS, and three waves that draw the noise of the next
+// kShortPhase commits while the consumer takes the current ones (two rounds of
+// their 192 lanes: 24 commits x 16 Philox blocks).  The consumer's chain is 25
+// vector instructions and no memory but LDS, read one commit ahead; a worker that
+// commits twice in a row hands its rows over in registers.  The consumer's place
+// among the block's waves, which the hardware spreads over the SIMDs, rotates
+// with the blocks of a compute unit.
+//
+// a.sched: the commits' slots, two 16-bit numbers a word; then each slot's worker;
+// the staleness values from kRunTauAt on; the number of slots in the last word.
+template <Variant V, bool BF16>
+__global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
+{
+    extern __shared__ float4 slot_lds[];
+    constexpr int kLanes = static_cast<int>(kShortElems);
+    constexpr bool FAST = V != Variant::General;
+    const bool global_m = V == Variant::FastGlobal ||
+                          (V == Variant::General && (a.mode & kModeGlobalProxy));
+    const bool adaptive = V == Variant::General && (a.mode & kModeAdaptive);
+    const int slots = static_cast<int>(a.sched[kRunWords - 1]);
+    float2* const rows = reinterpret_cast<float2*>(slot_lds);              // [slots][64]: (s, m)
+    float* const noise = reinterpret_cast<float*>(rows + slots * kLanes);  // [2][kShortPhase][64]
+    uint16_t* const slot_of = reinterpret_cast<uint16_t*>(noise + 2 * kShortPhase * kLanes);
+    uint32_t* const tau_of = reinterpret_cast<uint32_t*>(slot_of + short_sched_pad(a.K));
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int consumer = (blockIdx.x >> 8) & 3;
+    const int64_t blk0 = static_cast<int64_t>(blockIdx.x) * kLanes;        // (Pp: a multiple of 64)
+    float* const row0 = a.S + tile_index(a.nw, 0, blk0) + lane;
+    const uint32_t* const slot_worker = a.sched + (a.K + 1) / 2;
+
+    for (int j = threadIdx.x; j < a.K + 2; j += kBlock)
+        slot_of[j] = j < a.K ? static_cast<uint16_t>(a.sched[j >> 1] >> (16 * (j & 1))) : uint16_t{0};
+    if (adaptive)
+        for (int j = threadIdx.x; j < a.K; j += kBlock) tau_of[j] = a.sched[kRunTauAt + j];
+    for (int k = wave; k < slots; k += 4) {
+        const float* p = row0 + (static_cast<int64_t>(slot_worker[k]) << (kTileShift + 1));
+        rows[k * kLanes + lane] = make_float2(p[0], global_m ? 0.0f : p[kTileElems]);
+    }
+
+    // sigma z of commits j0 .. j0 + kShortPhase - 1, drawn by `threads` threads
+    auto draw = [&](int j0, float* out, int id, int threads) __attribute__((always_inline)) {
+        for (int k = id; k < kShortPhase * (kLanes / 4); k += threads) {
+            const int jj = k / (kLanes / 4);
+            const int q = k % (kLanes / 4);
+            const float4 z = normals4<false>(static_cast<uint64_t>(blk0 / 4 + q),
+                                             a.t0 + static_cast<uint32_t>(j0 + jj), a.key0, a.key1);
+            *reinterpret_cast<float4*>(out + jj * kLanes + 4 * q) =
+                make_float4(a.sigma * z.x, a.sigma * z.y, a.sigma * z.z, a.sigma * z.w);
+        }
+    };
+    draw(0, noise, threadIdx.x, kBlock);
+
+    float th = 0.0f, hh = 0.0f, tt = 0.0f, mg = 0.0f;
+    if (wave == consumer) {
+        th = a.theta[blk0 + lane];
+        hh = a.h[blk0 + lane];
+        tt = a.ts[blk0 + lane];
+        if (global_m) mg = row0[kTileElems];
+    }
+    __syncthreads();
+
+    uint32_t slot = slot_of[0], slot_next = slot_of[1];
+    float2 row = rows[slot * kLanes + lane];
+    for (int j0 = 0, half = 0; j0 < a.K; j0 += kShortPhase, half ^= 1) {
+        if (wave == consumer) {
+            const int n = a.K - j0 < kShortPhase ? a.K - j0 : kShortPhase;
+            const float* nz = noise + half * (kShortPhase * kLanes) + lane;
+            float z = nz[0];
+#pragma unroll 4
+            for (int i = 0; i < n; ++i) {
+                // what the next commit reads, before this one's rows are written
+                float2 row_next = rows[slot_next * kLanes + lane];
+                const uint32_t slot_after = slot_of[j0 + i + 2];
+                const float z_next = nz[(i + 1 < kShortPhase ? i + 1 : i) * kLanes];
+                const float s[1] = {row.x};
+                float d[1] = {a.neg_lr * __builtin_fmaf(hh, s[0] - tt, z)};
+                if (BF16) d[0] = __uint_as_float(pack_bf16(d[0], d[0]) << 16);
+                float t[1] = {th}, m[1] = {global_m ? mg : row.y}, snap[1];
+                if constexpr (FAST) {
+                    commit_fast<1, false>(a, d, s, t, m);
+                    snap[0] = t[0];
+                } else {
+                    const int tau = adaptive ? static_cast<int>(tau_of[j0 + i]) : 0;
+                    commit_general<1>(a, tau, d, s, t, m, snap);
+                }
+                th = t[0];
+                if (global_m) mg = m[0];
+                rows[slot * kLanes + lane] = make_float2(snap[0], m[0]);
+                const bool again = slot_next == slot;
+                row.x = again ? snap[0] : row_next.x;
+                row.y = again ? m[0] : row_next.y;
+                slot = slot_next;
+                slot_next = slot_after;
+                z = z_next;
+            }
+        } else if (j0 + kShortPhase < a.K) {
+            draw(j0 + kShortPhase, noise + (half ^ 1) * (kShortPhase * kLanes),
+                 ((wave - consumer - 1) & 3) * 64 + lane, kBlock - 64);
+        }
+        __syncthreads();
+    }
+    for (int k = wave; k < slots; k += 4) {
+        float* p = row0 + (static_cast<int64_t>(slot_worker[k]) << (kTileShift + 1));
+        const float2 r = rows[k * kLanes + lane];
+        p[0] = r.x;
+        if (!global_m) p[kTileElems] = r.y;
+    }
+    if (wave == consumer) {
+        a.theta[blk0 + lane] = th;
+        if (global_m) row0[kTileElems] = mg;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1610,6 +1756,39 @@ hipError_t launch_run(const RunArgs& a, Variant v, bool bf16_out, bool stream_ro
     case Variant::General: break;
     }
     return launch_run_v<Variant::General>(a, bf16_out, stream_rows, lds_bytes, stream);
+}
+
+hipError_t launch_short_run(const RunArgs& a, Variant v, bool bf16_out, hipStream_t stream)
+{
+    const uint32_t slots = a.sched[kRunWords - 1];
+    const bool adaptive = v == Variant::General && (a.mode & kModeAdaptive);
+    if (a.K < 1 || slots < 1 || slots > static_cast<uint32_t>(kShortSlots) || a.Pp % kShortElems != 0 ||
+        (a.K + 1) / 2 + static_cast<int>(slots) > (adaptive ? kRunTauAt : kRunWords - 1) ||
+        (adaptive && kRunTauAt + a.K > kRunWords - 1))
+        return hipErrorInvalidValue;
+    const uint32_t lds = short_run_lds(static_cast<int>(slots), a.K, adaptive);
+    const dim3 grid(static_cast<unsigned>(a.Pp / kShortElems)), block(kBlock);
+    switch (v) {
+    case Variant::Fast:
+        if (bf16_out)
+            hipLaunchKernelGGL((short_run_kernel<Variant::Fast, true>), grid, block, lds, stream, a);
+        else
+            hipLaunchKernelGGL((short_run_kernel<Variant::Fast, false>), grid, block, lds, stream, a);
+        break;
+    case Variant::FastGlobal:
+        if (bf16_out)
+            hipLaunchKernelGGL((short_run_kernel<Variant::FastGlobal, true>), grid, block, lds, stream, a);
+        else
+            hipLaunchKernelGGL((short_run_kernel<Variant::FastGlobal, false>), grid, block, lds, stream, a);
+        break;
+    case Variant::General:
+        if (bf16_out)
+            hipLaunchKernelGGL((short_run_kernel<Variant::General, true>), grid, block, lds, stream, a);
+        else
+            hipLaunchKernelGGL((short_run_kernel<Variant::General, false>), grid, block, lds, stream, a);
+        break;
+    }
+    return hipGetLastError();
 }
 
 template <bool DIAG, bool NT>

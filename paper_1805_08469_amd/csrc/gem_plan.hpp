@@ -205,4 +205,40 @@ inline void plan_run(const int32_t* worker, int k, int depth, int slots, uint32_
     for (int q = 0; q < depth; ++q) words[k + q] = 0u;
 }
 
+// ---- runs over short vectors: every worker's rows in LDS ------------------------
+constexpr int64_t kShortElems = 64;    // elements of a block
+constexpr int kShortPhase = 24;        // commits between two barriers
+constexpr int kShortSlots = 128;       // workers of a launch, at most
+// 16-bit schedule entries of k commits, with the two read ahead, in whole words.
+constexpr int short_sched_pad(int k) { return (k + 3) / 2 * 2; }
+// LDS of a block: the slots, two phases' noise, the schedule and the staleness values.
+constexpr uint32_t short_run_lds(int slots, int k, bool adaptive)
+{
+    return static_cast<uint32_t>(slots * kShortElems * 8 + 2 * kShortPhase * kShortElems * 4 +
+                                 short_sched_pad(k) * 2 + (adaptive ? k * 4 : 0));
+}
+
+// Schedule words of a run of k commits by at most kShortSlots workers: a 16-bit
+// slot a commit, two to a word, then each slot's worker, and the number of slots
+// (returned) in the last word.  slot_of is scratch of one int per worker (-1 on
+// entry and on return).
+inline int plan_short_run(const int32_t* worker, int k, uint32_t* words, int32_t* slot_of)
+{
+    uint32_t* const slot_worker = words + (k + 1) / 2;
+    if (k % 2) words[k / 2] = 0;
+    int slots = 0;
+    for (int j = 0; j < k; ++j) {
+        int32_t& slot = slot_of[worker[j]];
+        if (slot < 0) {
+            slot_worker[slots] = static_cast<uint32_t>(worker[j]);
+            slot = slots++;
+        }
+        if (j % 2) words[j / 2] |= static_cast<uint32_t>(slot) << 16;
+        else words[j / 2] = static_cast<uint32_t>(slot);
+    }
+    for (int j = 0; j < k; ++j) slot_of[worker[j]] = -1;
+    words[kRunWords - 1] = static_cast<uint32_t>(slots);
+    return slots;
+}
+
 }  // namespace gemk

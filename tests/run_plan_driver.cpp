@@ -102,6 +102,31 @@ int replay(const std::vector<int32_t>& w, int n, int depth, int slots)
     return held;
 }
 
+// A short vector's words: commit j's slot names commit j's worker, every worker
+// has one slot, and nothing past the schedule's parts is written.
+void check_short(const std::vector<int32_t>& w, int n)
+{
+    using namespace gemk;
+    const int k = static_cast<int>(w.size());
+    std::vector<uint32_t> words(kRunWords, 0xFFFFFFFFu);
+    std::vector<int32_t> slot_of(n, -1);
+    const int slots = plan_short_run(w.data(), k, words.data(), slot_of.data());
+    for (int v : slot_of)
+        if (v != -1) fail("short: scratch not restored", 0, k, slots);
+    if (words[kRunWords - 1] != static_cast<uint32_t>(slots)) fail("short: slot count", 0, k, slots);
+    const uint32_t* slot_worker = words.data() + (k + 1) / 2;
+    std::vector<int> seen(n, 0);
+    for (int q = 0; q < slots; ++q)
+        if (seen[slot_worker[q]]++) fail("short: a worker with two slots", q, k, slots);
+    for (int j = 0; j < k; ++j) {
+        const uint32_t s = (words[j / 2] >> (16 * (j % 2))) & 0xFFFFu;
+        if (static_cast<int>(s) >= slots || static_cast<int32_t>(slot_worker[s]) != w[j])
+            fail("short: slot", j, k, slots);
+    }
+    for (int q = (k + 1) / 2 + slots; q < kRunWords - 1; ++q)
+        if (words[q] != 0xFFFFFFFFu) fail("short: word past the end", q, k, slots);
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -124,6 +149,9 @@ int main(int argc, char** argv)
             default: w[j] = j % n; break;                                                 // round robin
             }
         }
+        std::vector<int32_t> few(w);
+        for (int32_t& x : few) x %= kShortSlots;
+        check_short(few, std::min(n, kShortSlots));
         const int held = replay(w, n, depth, slots), most = most_waits(w, slots);
         // Waits shorter than depth are kept whatever they push out, so a plan may
         // hold fewer than the optimum only where such waits are.

@@ -97,6 +97,67 @@ def test_adaptive_launch_lengths(G, T):
     _case(G, 200, 12, T, 4, _hp(G, rule=G.GEM_RULE_ADAPTIVE))
 
 
+@pytest.mark.parametrize("T", [23, 24, 25, 48, 49])
+@pytest.mark.parametrize("n,P", [(1, 64), (2, 65), (5, 129)])
+def test_short_vector_phases(G, T, n, P):
+    """The short-vector kernel at the edges of its phases of 24 commits and of its
+    blocks of 64 elements, with workers that commit twice in a row."""
+    _case(G, P, n, T, 1, _hp(G), bf16=(T == 25))
+
+
+@pytest.mark.parametrize("n", [127, 128, 129])
+def test_short_vector_worker_limit(G, n):
+    """128 workers' rows are held in LDS; a launch of more takes the other kernel."""
+    from paper_1805_08469_amd.workloads import make_problem
+    P, T = 700, 1500
+    h, ts = make_problem(P, 1e-3, 1.0, 3)
+    worker = np.arange(T, dtype=np.int32) * 7 % n
+    hp = _hp(G)
+    st = _oracle(G, hp, P, n, worker, None, h, ts, False)
+    with G.Gem(P, n, hp) as g:
+        g.set_quadratic(h, ts, 0.01, 0.1, 77)
+        g.sim_run(worker, None, 8)
+        assert_parity("theta", g.theta(), st.theta)
+        assert_parity("S", g.S(), st.S)
+        assert_parity("M", g.M(), st.M)
+
+
+LONG = [("kappa", 9, 520, False), ("adaptive", 9, 991, True), ("adaptive", 5, 496, False),
+        ("downpour", 9, 130, True), ("pre_pull", 9, 520, False), ("tiny_eps", 9, 130, True),
+        ("shared_kappa", 14, 300, False), ("shared_pre_pull", 9, 300, True),
+        ("shared_tiny_eps", 9, 300, False), ("default", 1, 40, False), ("default", 5, 600, True),
+        ("default", 7, 993, False), ("default", 11, 994, False), ("default", 101, 600, True),
+        ("shared", 10, 600, False), ("shared", 11, 600, True), ("default", 20, 3, False)]
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2])
+@pytest.mark.parametrize("mode,n,T,bf16", LONG)
+def test_long_vectors(G, mode, n, T, bf16, policy):
+    """Vectors too long for the short-vector kernel: the run kernel, compared at
+    the vector's ends and about its tiles' and blocks' edges."""
+    import torch
+    from paper_1805_08469_amd.workloads import make_problem
+    P = 64 * 8 * torch.cuda.get_device_properties(0).multi_processor_count + 1029
+    hp = _hp(G, **{**MODES, "default": {}, "shared": dict(proxy_mode=1)}[mode])
+    h, ts = make_problem(P, 1e-3, 1.0, 3)
+    worker, tau = G.gem_schedule_make(n, T, 0, 0.0, 0.0, seed=n + T, pull_mode=hp.pull_mode)
+    idx = np.unique(np.concatenate([np.arange(0, 1100), np.arange(8100, 8300), np.arange(P - 1100, P)]))
+    ohp = O.Hyper(lr=0.01, sigma=0.1, momentum=hp.momentum, eps=hp.eps, kappa=hp.kappa,
+                  pi_mode=hp.pi_mode, kappa_mode=hp.kappa_mode, pull_mode=hp.pull_mode,
+                  rule=hp.rule, bf16=bf16, proxy=hp.proxy_mode, seed=77)
+    st = O.State.initial(n, idx.size)
+    O.run(ohp, P, st, idx, h[idx], ts[idx], worker, tau)
+    print(f"[long] {mode} n={n} T={T} bf16={bf16} policy={policy} P={P}", flush=True)
+    with G.Gem(P, n, hp) as g:
+        g.set_cache_policy(policy)
+        g.set_quadratic(h, ts, 0.01, 0.1, 77, bf16=bf16)
+        g.sim_run(worker, tau, 1)
+        theta, S, M = g.gather(idx)
+        assert_parity("theta", theta, st.theta)
+        assert_parity("S", S, st.S)
+        assert_parity("M", M, st.M)
+
+
 @pytest.mark.parametrize("policy", [1, 2])
 @pytest.mark.parametrize("proxy", [0, 1])
 def test_policies_and_heavy_tails(G, policy, proxy):

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "gem_device.hpp"
 #include "gem_internal.hpp"
@@ -759,24 +760,33 @@ __global__ __launch_bounds__(kBlock) void pass_kernel(const PassArgs a)
     }
 }
 
-// The general rule's step on a thread's W elements (run kernel, General
-// variant): commit_element's arithmetic, every mode a uniform runtime flag,
-// with one range check for the W quotients as in commit_fast.
-template <int W>
+// Mode bits of the General variant's kernels of a run: those of the launch
+// (kAnyMode), or one rule's known when compiled (then eps >= 2^-60).  With the
+// modes as uniform runtime flags the step is cut by their branches and the noise
+// no longer fills its latencies: kappa = 2, 3141593 elements, 30 workers, 500
+// commits 2.65 ms, with a kernel of its own 2.47; 65536 elements, 400 commits 236
+// and 203 us.
+constexpr uint32_t kAnyMode = ~0u;
+
+// The general rule's step on a thread's W elements (run kernels, General
+// variant): commit_element's arithmetic, with one range check for the W
+// quotients as in commit_fast.
+template <int W, uint32_t MODE>
 __device__ __forceinline__ void commit_general(const RunArgs& a, int tau, const float (&d)[W],
                                                const float (&s)[W], float (&th)[W], float (&m)[W],
                                                float (&snap)[W])
 {
+    const uint32_t mode = MODE == kAnyMode ? a.mode : MODE;
     float next[W];
 #pragma unroll
     for (int k = 0; k < W; ++k) m[k] = __builtin_fmaf(a.mu, m[k], d[k]);
-    if (a.mode & kModeDownpour) {
+    if (mode & kModeDownpour) {
 #pragma unroll
         for (int k = 0; k < W; ++k) next[k] = th[k] + d[k];         // eq. 1
     } else {
         // num / den: the scale factor (eq. 18), or the damped update itself
-        const bool adaptive = (a.mode & kModeAdaptive) != 0;
-        const float k_eff = (a.mode & kModeKappaMul) ? a.k_eff : 1.0f;
+        const bool adaptive = (mode & kModeAdaptive) != 0;
+        const float k_eff = (mode & kModeKappaMul) ? a.k_eff : 1.0f;
         const float stale = static_cast<float>(tau + 1);
         float num[W], den[W], q[W];
 #pragma unroll
@@ -787,10 +797,12 @@ __device__ __forceinline__ void commit_general(const RunArgs& a, int tau, const 
         }
         float lo, hi;
         magnitudes(num, den, lo, hi);
-        keep(hi);
-        if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
+        if constexpr (MODE == kAnyMode) {
+            keep(hi);
+            if (__float_as_uint(a.eps) < __float_as_uint(0x1p-60f)) {
 #pragma unroll
-            for (int k = 0; k < W; ++k) lo = __builtin_fminf(lo, den[k]);
+                for (int k = 0; k < W; ++k) lo = __builtin_fminf(lo, den[k]);
+            }
         }
 #pragma unroll
         for (int k = 0; k < W; ++k) q[k] = div_rn_core(num[k], den[k]);
@@ -802,7 +814,7 @@ __device__ __forceinline__ void commit_general(const RunArgs& a, int tau, const 
 #pragma unroll
             for (int k = 0; k < W; ++k) next[k] = th[k] + q[k];
         } else {
-            const bool literal = (a.mode & kModeLiteralPi) != 0;
+            const bool literal = (mode & kModeLiteralPi) != 0;
 #pragma unroll
             for (int k = 0; k < W; ++k) {
                 const float pi = literal ? q[k] : __builtin_amdgcn_fmed3f(q[k], 0.0f,
@@ -813,18 +825,19 @@ __device__ __forceinline__ void commit_general(const RunArgs& a, int tau, const 
     }
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        snap[k] = (a.mode & kModePrePull) ? th[k] : next[k];
+        snap[k] = (mode & kModePrePull) ? th[k] : next[k];
         th[k] = next[k];
     }
 }
 
+template <uint32_t MODE>
 __device__ __forceinline__ void commit4_general(const RunArgs& a, int tau, const float4& d,
                                                 const float4& s, float4& th, float4& m,
                                                 float4& snap)
 {
     const float dv[4] = {d.x, d.y, d.z, d.w}, sv[4] = {s.x, s.y, s.z, s.w};
     float tv[4] = {th.x, th.y, th.z, th.w}, mv[4] = {m.x, m.y, m.z, m.w}, nv[4];
-    commit_general<4>(a, tau, dv, sv, tv, mv, nv);
+    commit_general<4, MODE>(a, tau, dv, sv, tv, mv, nv);
     th = make_float4(tv[0], tv[1], tv[2], tv[3]);
     snap = make_float4(nv[0], nv[1], nv[2], nv[3]);
     m = make_float4(mv[0], mv[1], mv[2], mv[3]);
@@ -882,13 +895,14 @@ __device__ __forceinline__ void put_row_at(float* base, bool mem, uint32_t byte_
 // faster with all rows in LDS).  Chunks wait in LDS rather than in registers:
 // 8 register slots beside 6 in LDS, selected by uniform branches, moved a
 // quarter less but ran 2% slower.
-template <Variant V, bool BF16, int DEPTH, bool NT>
+template <Variant V, bool BF16, int DEPTH, bool NT, uint32_t MODE>
 __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
 {
     extern __shared__ float4 slot_lds[];   // [slots][1 or 2 rows][kBlock]
     constexpr bool SHARED = V == Variant::FastGlobal;       // only snapshots move
     constexpr int kSlotRows = SHARED ? 1 : 2;
-    const bool global_m = SHARED || (V == Variant::General && (a.mode & kModeGlobalProxy));
+    const uint32_t mode = MODE == kAnyMode ? a.mode : MODE;
+    const bool global_m = SHARED || (V == Variant::General && (mode & kModeGlobalProxy));
     const int64_t grp = blockIdx.x;
     const int64_t c = grp * kBlock + threadIdx.x;
     if (c >= (a.Pp >> 2)) return;
@@ -942,9 +956,9 @@ __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
         z = noise(j + 1);
         float4 snap;
         if constexpr (V == Variant::General) {
-            const int tau = (a.mode & kModeAdaptive)
+            const int tau = (mode & kModeAdaptive)
                                 ? static_cast<int>(a.sched[kRunTauAt + j]) : 0;
-            commit4_general(a, tau, d, rows.s, th, m, snap);
+            commit4_general<MODE>(a, tau, d, rows.s, th, m, snap);
         } else {
             commit4_fast<false>(a, d, rows.s, th, m, snap);
         }
@@ -990,15 +1004,16 @@ __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
 //
 // a.sched: the commits' slots, two 16-bit numbers a word; then each slot's worker;
 // the staleness values from kRunTauAt on; the number of slots in the last word.
-template <Variant V, bool BF16>
+template <Variant V, bool BF16, uint32_t MODE>
 __global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
 {
     extern __shared__ float4 slot_lds[];
     constexpr int kLanes = static_cast<int>(kShortElems);
     constexpr bool FAST = V != Variant::General;
+    const uint32_t mode = MODE == kAnyMode ? a.mode : MODE;
     const bool global_m = V == Variant::FastGlobal ||
-                          (V == Variant::General && (a.mode & kModeGlobalProxy));
-    const bool adaptive = V == Variant::General && (a.mode & kModeAdaptive);
+                          (V == Variant::General && (mode & kModeGlobalProxy));
+    const bool adaptive = V == Variant::General && (mode & kModeAdaptive);
     const int slots = static_cast<int>(a.sched[kRunWords - 1]);
     float2* const rows = reinterpret_cast<float2*>(slot_lds);              // [slots][64]: (s, m)
     float* const noise = reinterpret_cast<float*>(rows + slots * kLanes);  // [2][kShortPhase][64]
@@ -1064,7 +1079,7 @@ __global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
                     snap[0] = t[0];
                 } else {
                     const int tau = adaptive ? static_cast<int>(tau_of[j0 + i]) : 0;
-                    commit_general<1>(a, tau, d, s, t, m, snap);
+                    commit_general<1, MODE>(a, tau, d, s, t, m, snap);
                 }
                 th = t[0];
                 if (global_m) mg = m[0];
@@ -1724,23 +1739,29 @@ hipError_t launch_pass(const PassArgs& a, Source src, Variant v, bool bf16_out, 
 
 namespace {
 
-template <Variant V, bool BF16, bool NT>
-hipError_t launch_run_one(const RunArgs& a, uint32_t lds, hipStream_t stream)
+// Calls f(V, MODE) (as integral constants) with a run's specialisation: the
+// default rule's variants, and of the general ones those whose single mode has
+// its own kernel (kappa, the pre-commit pull, adaptive staleness, each with
+// per-worker moments).
+template <typename F>
+hipError_t with_run_rule(const RunArgs& a, Variant v, F f)
 {
-    hipLaunchKernelGGL((run_kernel<V, BF16, kRunDepth, NT>), dim3(blocks_for(a.Pp >> 2)), dim3(kBlock),
-                       lds, stream, a);
-    return hipGetLastError();
-}
-
-template <Variant V>
-hipError_t launch_run_v(const RunArgs& a, bool bf16_out, bool stream_rows, uint32_t lds,
-                        hipStream_t stream)
-{
-    if (bf16_out)
-        return stream_rows ? launch_run_one<V, true, true>(a, lds, stream)
-                           : launch_run_one<V, true, false>(a, lds, stream);
-    return stream_rows ? launch_run_one<V, false, true>(a, lds, stream)
-                       : launch_run_one<V, false, false>(a, lds, stream);
+    using AnyMode = std::integral_constant<uint32_t, kAnyMode>;
+    using General = std::integral_constant<Variant, Variant::General>;
+    switch (v) {
+    case Variant::Fast: return f(std::integral_constant<Variant, Variant::Fast>{}, AnyMode{});
+    case Variant::FastGlobal: return f(std::integral_constant<Variant, Variant::FastGlobal>{}, AnyMode{});
+    case Variant::General: break;
+    }
+    if (a.eps >= 0x1p-60f) {
+        switch (a.mode) {
+        case kModeKappaMul: return f(General{}, std::integral_constant<uint32_t, kModeKappaMul>{});
+        case kModePrePull: return f(General{}, std::integral_constant<uint32_t, kModePrePull>{});
+        case kModeAdaptive: return f(General{}, std::integral_constant<uint32_t, kModeAdaptive>{});
+        default: break;
+        }
+    }
+    return f(General{}, AnyMode{});
 }
 
 }  // namespace
@@ -1749,13 +1770,20 @@ hipError_t launch_run(const RunArgs& a, Variant v, bool bf16_out, bool stream_ro
                       uint32_t lds_bytes, hipStream_t stream)
 {
     if (a.K < 1 || a.K > kRunCommits) return hipErrorInvalidValue;
-    switch (v) {
-    case Variant::Fast: return launch_run_v<Variant::Fast>(a, bf16_out, stream_rows, lds_bytes, stream);
-    case Variant::FastGlobal:
-        return launch_run_v<Variant::FastGlobal>(a, bf16_out, stream_rows, lds_bytes, stream);
-    case Variant::General: break;
-    }
-    return launch_run_v<Variant::General>(a, bf16_out, stream_rows, lds_bytes, stream);
+    const dim3 grid(blocks_for(a.Pp >> 2)), block(kBlock);
+    return with_run_rule(a, v, [&](auto rule, auto rule_mode) {
+        constexpr Variant V = decltype(rule)::value;
+        constexpr uint32_t MODE = decltype(rule_mode)::value;
+        if (bf16_out && stream_rows)
+            hipLaunchKernelGGL((run_kernel<V, true, kRunDepth, true, MODE>), grid, block, lds_bytes, stream, a);
+        else if (bf16_out)
+            hipLaunchKernelGGL((run_kernel<V, true, kRunDepth, false, MODE>), grid, block, lds_bytes, stream, a);
+        else if (stream_rows)
+            hipLaunchKernelGGL((run_kernel<V, false, kRunDepth, true, MODE>), grid, block, lds_bytes, stream, a);
+        else
+            hipLaunchKernelGGL((run_kernel<V, false, kRunDepth, false, MODE>), grid, block, lds_bytes, stream, a);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_short_run(const RunArgs& a, Variant v, bool bf16_out, hipStream_t stream)
@@ -1768,27 +1796,13 @@ hipError_t launch_short_run(const RunArgs& a, Variant v, bool bf16_out, hipStrea
         return hipErrorInvalidValue;
     const uint32_t lds = short_run_lds(static_cast<int>(slots), a.K, adaptive);
     const dim3 grid(static_cast<unsigned>(a.Pp / kShortElems)), block(kBlock);
-    switch (v) {
-    case Variant::Fast:
-        if (bf16_out)
-            hipLaunchKernelGGL((short_run_kernel<Variant::Fast, true>), grid, block, lds, stream, a);
-        else
-            hipLaunchKernelGGL((short_run_kernel<Variant::Fast, false>), grid, block, lds, stream, a);
-        break;
-    case Variant::FastGlobal:
-        if (bf16_out)
-            hipLaunchKernelGGL((short_run_kernel<Variant::FastGlobal, true>), grid, block, lds, stream, a);
-        else
-            hipLaunchKernelGGL((short_run_kernel<Variant::FastGlobal, false>), grid, block, lds, stream, a);
-        break;
-    case Variant::General:
-        if (bf16_out)
-            hipLaunchKernelGGL((short_run_kernel<Variant::General, true>), grid, block, lds, stream, a);
-        else
-            hipLaunchKernelGGL((short_run_kernel<Variant::General, false>), grid, block, lds, stream, a);
-        break;
-    }
-    return hipGetLastError();
+    return with_run_rule(a, v, [&](auto rule, auto rule_mode) {
+        constexpr Variant V = decltype(rule)::value;
+        constexpr uint32_t MODE = decltype(rule_mode)::value;
+        if (bf16_out) hipLaunchKernelGGL((short_run_kernel<V, true, MODE>), grid, block, lds, stream, a);
+        else hipLaunchKernelGGL((short_run_kernel<V, false, MODE>), grid, block, lds, stream, a);
+        return hipGetLastError();
+    });
 }
 
 template <bool DIAG, bool NT>

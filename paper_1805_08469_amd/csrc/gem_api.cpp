@@ -325,12 +325,16 @@ struct RunShape {
 //   - 4 blocks of 5 (10) slots when that holds every worker: nothing moves, and
 //     four waves per SIMD issue best (5 workers: 13.2 ms, 13.8 ms with 3 blocks,
 //     16.2 with 2);
-//   - up to 100 workers 3 blocks (10 workers: 15.6, 2 blocks 16.2; 64 workers
+//   - then 3 blocks (10 workers: 15.6, 2 blocks 16.2; 64 workers
 //     equal; 100 workers 21.4, 2 blocks 21.2);
 //   - beyond, 2 blocks of 10 slots: fewer rows move, and the rows in flight have
 //     larger shares of the Infinity Cache (150 workers: 21.7, 3 blocks 25.2; 300:
 //     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
-//     (300 workers: 17.2, 2 blocks 18.1).
+//     (300 workers: 17.2, 2 blocks 18.1);
+//   - from 61 workers on the same over 8M parameters or more, where the blocks are
+//     many rounds (124M parameters, 64 workers, 160 commits with bf16 updates: 37.6,
+//     3 blocks 40.7; 25M, 64 workers, 990 commits: 37.5, 38.4; 100 workers: 40.3,
+//     41.2); 4M with 100 workers keep 3 (400 commits: 2.77, 2 blocks 2.93).
 // Rows stream when few of them are found in the Infinity Cache again: beyond
 // 250 workers (300: 26.5 ms, default policy 27.2; 200: 24.5, 23.6), or when a
 // worker commits fewer than 1.4 times in the launch (25M parameters, 100
@@ -340,7 +344,9 @@ RunShape run_shape(const gem_handle* g, gemk::Variant v, int64_t k, int64_t dist
     const int all = static_cast<int>(std::min<int64_t>(g->lds_per_cu, 160 << 10)) / gemk::run_slot_bytes(v);
     int blocks = 3;
     if (distinct <= all / 4) blocks = 4;
-    else if (distinct > 100 && v != gemk::Variant::FastGlobal) blocks = 2;
+    else if (v != gemk::Variant::FastGlobal &&
+             (distinct > 100 || (distinct > 60 && g->Pp >= (int64_t{8} << 20))))
+        blocks = 2;
     RunShape r;
     r.slots = std::min(std::max(all / blocks, gemk::kRunDepth), gemk::kRunMaxSlots);
     if (g->cache_policy != GEM_CACHE_AUTO) r.stream = g->cache_policy == GEM_CACHE_STREAM;
@@ -356,7 +362,7 @@ RunShape run_shape(const gem_handle* g, gemk::Variant v, int64_t k, int64_t dist
 // (400 commits and the reads after them, short and run kernel, us): 20 workers,
 // 65536 elements 199 and 342, 131072: 257 and 345, 262144: 341 and 351, 524288:
 // 522 and 438; 100 workers, 32768: 192 and 343, 65536: 261 and 343, 131072: 386 and
-// 347; kappa = 2, 131072: 322 and 421, 262144: 440 and 423.
+// 347; kappa = 2, 131072: 255 and 421.
 bool short_run(const gem_handle* g, int64_t distinct, int k, bool adaptive)
 {
     if (distinct > gemk::kShortSlots) return false;

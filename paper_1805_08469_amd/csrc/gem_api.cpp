@@ -56,9 +56,9 @@ struct gem_handle {
     int64_t* part_off = nullptr;     // [nseg + 1]
     int32_t* gseg = nullptr;         // [groups]
     double* part = nullptr;          // [3][npart][4] wave sums of the current commit
-    int32_t* pair_seg = nullptr;     // [nsup] (segment, index block) pairs
-    int32_t* pair_blk = nullptr;
-    int64_t* sup_off = nullptr;      // [nseg + 1] first index-block slot of each segment
+    gemk::SegUnit* units = nullptr;  // [nunits] what each block of the upper levels adds up
+    int64_t nunits = 0;
+    int32_t seg_teams = 1;           // teams of 256 threads in such a block
     double* sup = nullptr;           // [3][nsup] index-block sums
     float* pi_seg = nullptr;         // [nseg]
     uint32_t* seg_done = nullptr;    // [nseg] pair blocks finished in the running launch
@@ -460,18 +460,17 @@ void free_segments(gem_handle* g)
     (void)hipFree(g->part_off);
     (void)hipFree(g->gseg);
     (void)hipFree(g->part);
-    (void)hipFree(g->pair_seg);
-    (void)hipFree(g->pair_blk);
-    (void)hipFree(g->sup_off);
+    (void)hipFree(g->units);
     (void)hipFree(g->sup);
     (void)hipFree(g->pi_seg);
     (void)hipFree(g->seg_done);
     g->seg_done = nullptr;
-    g->seg_off = g->part_off = g->sup_off = nullptr;
-    g->gseg = g->pair_seg = g->pair_blk = nullptr;
+    g->seg_off = g->part_off = nullptr;
+    g->gseg = nullptr;
+    g->units = nullptr;
     g->part = g->sup = nullptr;
     g->pi_seg = nullptr;
-    g->npart = g->nsup = 0;
+    g->npart = g->nsup = g->nunits = 0;
     g->seg_host.clear();
 }
 
@@ -483,17 +482,31 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
     std::vector<int64_t> part_off(static_cast<size_t>(nseg) + 1, 0);
     for (int32_t k = 0; k < nseg; ++k)
         part_off[k + 1] = part_off[k] + (off[k + 1] - 1) / gemk::kSegGroup - off[k] / gemk::kSegGroup + 1;
-    std::vector<int64_t> sup_off(static_cast<size_t>(nseg) + 1, 0);
-    std::vector<int32_t> pair_seg, pair_blk;
-    for (int32_t s = 0; s < nseg; ++s) {
-        const int64_t b_lo = off[s] / gemk::kSegBlock, b_hi = (off[s + 1] - 1) / gemk::kSegBlock;
-        sup_off[s + 1] = sup_off[s] + (b_hi - b_lo + 1);
-        for (int64_t b = b_lo; b <= b_hi; ++b) {
-            pair_seg.push_back(s);
-            pair_blk.push_back(static_cast<int32_t>(b));
+    auto index_blocks = [&](int32_t k) {
+        return (off[k + 1] - 1) / gemk::kSegBlock - off[k] / gemk::kSegBlock + 1;
+    };
+    int64_t nsup = 0, most = 0;
+    for (int32_t k = 0; k < nseg; ++k) most = std::max(most, index_blocks(k));
+    const int teams = most > 1 && nseg <= gemk::kSegUnitMost ? gemk::kSegTeams : 1;
+    std::vector<gemk::SegUnit> units;
+    for (int32_t k = 0; k < nseg; ++k) {
+        gemk::SegUnit u{};
+        u.part_first = part_off[k];
+        u.g_lo = off[k] / gemk::kSegGroup;
+        u.g_hi = (off[k + 1] - 1) / gemk::kSegGroup;
+        u.size = off[k + 1] - off[k];
+        u.sup_first = nsup;
+        u.sup_count = index_blocks(k);
+        u.units = static_cast<int32_t>((u.sup_count + teams - 1) / teams);
+        u.seg = k;
+        for (int64_t b = 0; b < u.sup_count; b += teams) {
+            u.sup_at = nsup + b;
+            u.blk0 = off[k] / gemk::kSegBlock + b;
+            u.nblk = static_cast<int32_t>(std::min<int64_t>(teams, u.sup_count - b));
+            units.push_back(u);
         }
+        nsup += u.sup_count;
     }
-    const int64_t nsup = sup_off[nseg];
     std::vector<int32_t> gseg(static_cast<size_t>(groups));
     int32_t k = 0;
     for (int64_t grp = 0; grp < groups; ++grp) {
@@ -508,9 +521,7 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
               hipMalloc(&g->gseg, gseg.size() * sizeof(int32_t)) == hipSuccess &&
               hipMalloc(&g->part, static_cast<size_t>(3 * npart * gemk::kWavesPerGroup) *
                                       sizeof(double)) == hipSuccess &&
-              hipMalloc(&g->pair_seg, pair_seg.size() * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&g->pair_blk, pair_blk.size() * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&g->sup_off, sup_off.size() * sizeof(int64_t)) == hipSuccess &&
+              hipMalloc(&g->units, units.size() * sizeof(gemk::SegUnit)) == hipSuccess &&
               hipMalloc(&g->sup, static_cast<size_t>(3 * nsup) * sizeof(double)) == hipSuccess &&
               hipMalloc(&g->pi_seg, static_cast<size_t>(nseg) * sizeof(float)) == hipSuccess &&
               hipMalloc(&g->seg_done, static_cast<size_t>(nseg) * sizeof(uint32_t)) == hipSuccess;
@@ -521,6 +532,8 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
     }
     g->npart = npart;
     g->nsup = nsup;
+    g->nunits = static_cast<int64_t>(units.size());
+    g->seg_teams = teams;
     const int rc = [&]() -> int {
         GEM_HIP(hipMemcpyAsync(g->seg_off, off.data(), off.size() * sizeof(int64_t),
                                hipMemcpyHostToDevice, g->stream));
@@ -528,11 +541,7 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
                                hipMemcpyHostToDevice, g->stream));
         GEM_HIP(hipMemcpyAsync(g->gseg, gseg.data(), gseg.size() * sizeof(int32_t),
                                hipMemcpyHostToDevice, g->stream));
-        GEM_HIP(hipMemcpyAsync(g->pair_seg, pair_seg.data(), pair_seg.size() * sizeof(int32_t),
-                               hipMemcpyHostToDevice, g->stream));
-        GEM_HIP(hipMemcpyAsync(g->pair_blk, pair_blk.data(), pair_blk.size() * sizeof(int32_t),
-                               hipMemcpyHostToDevice, g->stream));
-        GEM_HIP(hipMemcpyAsync(g->sup_off, sup_off.data(), sup_off.size() * sizeof(int64_t),
+        GEM_HIP(hipMemcpyAsync(g->units, units.data(), units.size() * sizeof(gemk::SegUnit),
                                hipMemcpyHostToDevice, g->stream));
         GEM_HIP(hipMemsetAsync(g->seg_done, 0, static_cast<size_t>(nseg) * sizeof(uint32_t),
                                g->stream));
@@ -624,9 +633,8 @@ int run_segments(gem_handle* g, const int32_t* worker, int64_t T, Source src,
         f.hist = nullptr;
         if (g->hist_on && g->hist_count < g->hist_cap)
             f.hist = g->pi_hist + g->hist_count * g->hist_rows * GEM_PI_BINS;
-        GEM_HIP(gemk::launch_seg_blocks(g->part, g->npart, g->part_off, g->seg_off, g->pair_seg,
-                                        g->pair_blk, g->nsup, g->sup, g->sup_off, g->seg_done, f,
-                                        g->stream));
+        GEM_HIP(gemk::launch_seg_units(g->part, g->npart, g->units, g->nunits, g->seg_teams, g->sup,
+                                       g->nsup, g->seg_done, f, g->stream));
         if (g->hist_on) g->hist_count += 1;
         if (g->diag_on) g->diag_commits += 1;
         g->pc[w] = next_pull(g, t);

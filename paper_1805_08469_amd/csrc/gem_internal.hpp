@@ -95,7 +95,7 @@ static_assert(sizeof(RunArgs) <= 4096, "the argument block fits");
 // Segment-norm scale factors.  A sum of squares is the adjacent-pairs tree
 // over aligned blocks of kSegBlock indices, then the blocks in order.  The
 // step kernel forms the tree's lower levels, one aligned group of
-// kSegGroup = 4 * 256 indices per thread block; seg_blocks_kernel the upper
+// kSegGroup = 4 * 256 indices per thread block; seg_units_kernel the upper
 // levels, 256 groups per index block.
 constexpr int64_t kSegGroup = 1024;
 constexpr int64_t kSegBlock = 1 << 18;
@@ -177,7 +177,7 @@ constexpr int64_t kInfinityCacheBytes = int64_t{256} << 20;
 // stream_rows as for launch_pass (the diagnostic variant ignores it).
 hipError_t launch_seg_step(const SegArgs& a, Source src, bool bf16_out, bool stream_rows,
                            hipStream_t stream);
-// What the last block of each segment needs to form the segment's factor.
+// What the block that forms a segment's factor needs to form the segment's factor.
 struct SegFactors {
     float* pi_seg;        // [nseg] out
     float k_eff, eps;
@@ -186,12 +186,29 @@ struct SegFactors {
     uint32_t* hist;       // this commit's histogram rows, or null
     double* diag;         // [4] accumulators, or null
 };
+// The part of a segment that one block of seg_units_kernel adds up: up to
+// `teams` consecutive index blocks (kSegBlock indices each) of it.
+struct SegUnit {
+    int64_t part_first;   // the segment's first slot of group sums
+    int64_t g_lo, g_hi;   // the segment's first and last group
+    int64_t size;         // the segment's elements
+    int64_t sup_at;       // where this unit's index-block sums go
+    int64_t sup_first;    // the segment's first index-block sum,
+    int64_t sup_count;    // and how many it has
+    int64_t blk0;         // the unit's first index block
+    int32_t nblk;         // and how many it has
+    int32_t units;        // units of the segment
+    int32_t seg;
+    int32_t pad_;
+};
+// Teams of 256 threads in a block, unless no segment has more than one index block
+// or there are too many segments (kSegUnitMost) for blocks of 1024 threads: then 1.
+constexpr int kSegTeams = 4;
+constexpr int64_t kSegUnitMost = 1024;
 // seg_done: [nseg] counters, zero between launches (each launch leaves them zero).
-hipError_t launch_seg_blocks(const double* part, int64_t npart, const int64_t* part_off,
-                             const int64_t* seg_off, const int32_t* pair_seg,
-                             const int32_t* pair_blk, int64_t npairs, double* sup,
-                             const int64_t* sup_off, uint32_t* seg_done, const SegFactors& f,
-                             hipStream_t stream);
+hipError_t launch_seg_units(const double* part, int64_t npart, const SegUnit* units,
+                            int64_t nunits, int teams, double* sup, int64_t nsup,
+                            uint32_t* seg_done, const SegFactors& f, hipStream_t stream);
 hipError_t launch_generate(const float* S, int64_t nw, int32_t w, const float* h,
                            const float* ts, void* out, bool bf16, int64_t P, uint32_t t,
                            uint32_t key0, uint32_t key1, float neg_lr, float sigma,

@@ -1064,7 +1064,6 @@ __global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
             const int n = a.K - j0 < kShortPhase ? a.K - j0 : kShortPhase;
             const float* nz = noise + half * (kShortPhase * kLanes) + lane;
             float z = nz[0];
-#pragma unroll 4
             for (int i = 0; i < n; ++i) {
                 // what the next commit reads, before this one's rows are written
                 float2 row_next = rows[slot_next * kLanes + lane];
@@ -1114,7 +1113,7 @@ __global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
 // A commit's pi needs sums of squares over whole segments, so each commit is
 // split in two launches: the step kernel starts commit t (forms d, m and the
 // drift, stores m, writes each 1024-index group's tree sums of squares), and
-// seg_blocks_kernel adds the group sums of each 2^18-index block by the same
+// seg_units_kernel adds the group sums of each 2^18-index block by the same
 // tree, after which the last block of each segment adds the block sums in
 // order and forms the segment's pi.  The next step kernel applies those
 // factors (and the pull) before starting the next commit, generating the
@@ -1147,29 +1146,6 @@ __device__ __forceinline__ double block_tree_sum(double v, double* lds)
     const double r = (lds[0] + lds[1]) + (lds[2] + lds[3]);
     __syncthreads();
     return r;
-}
-
-// Three such sums at once, each in the same order as block_tree_sum, with one
-// pair of barriers for the three.
-__device__ __forceinline__ void block_tree_sum3(double& x, double& y, double& z, double (*lds)[4])
-{
-#pragma unroll
-    for (int mask = 1; mask < 64; mask <<= 1) {
-        x = x + __shfl_xor(x, mask);
-        y = y + __shfl_xor(y, mask);
-        z = z + __shfl_xor(z, mask);
-    }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        lds[0][wave] = x;
-        lds[1][wave] = y;
-        lds[2][wave] = z;
-    }
-    __syncthreads();
-    x = (lds[0][0] + lds[0][1]) + (lds[0][2] + lds[0][3]);
-    y = (lds[1][0] + lds[1][1]) + (lds[1][2] + lds[1][3]);
-    z = (lds[2][0] + lds[2][1]) + (lds[2][2] + lds[2][3]);
-    __syncthreads();
 }
 
 // No occupancy hint: with no barrier in the kernel, the compiler's own
@@ -1347,7 +1323,7 @@ void seg_step_kernel(const SegArgs a)
             cd = (xd[0] + xd[1]) + (xd[2] + xd[3]);
         }
         // The wave's 256-index subtree (lane butterflies add pairs 2k, 2k+1,
-        // then pairs of pairs, ...); seg_blocks_kernel adds the group's four
+        // then pairs of pairs, ...); seg_units_kernel adds the group's four
         // wave sums as (w0 + w1) + (w2 + w3), the next level of the same
         // tree.  No barrier: each wave writes its own slot.
 #pragma unroll
@@ -1376,119 +1352,137 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One wave (threadIdx.x < 64): add segment seg's index-block sums in
-// increasing order (the lanes load 64 at a time into LDS; lane 0 adds them
-// in order), take the norms (binary64 square root,
-// rounded to binary32) and form pi as in the element step (eq. 18 with norms).
-__device__ void reduce_segment(int32_t seg, const double* sup, int64_t nsup,
-                               const int64_t* __restrict__ sup_off, float* __restrict__ pi_seg,
-                               float k_eff, float eps, int32_t literal,
-                               const int64_t* __restrict__ seg_off, uint32_t* hist,
-                               int32_t hist_per_seg, double* diag, double (*tail)[64])
+// The factor of segment seg from its sums of squares of the drift, the moment
+// and the update, which lanes 0 to 2 of one whole wave hold as `sum`: the norms
+// (binary64 square roots, rounded to binary32), then pi as in the element step
+// (eq. 18 with norms).
+__device__ void segment_factor(int32_t seg, int64_t size, double sum, const SegFactors& f)
 {
-    const int64_t q0 = sup_off[seg], q1 = sup_off[seg + 1];
-    double sa = 0.0, sm = 0.0, sd = 0.0;
-    for (int64_t base = q0; base < q1; base += 64) {
-        // the lanes load 64 block sums of each kind at once into LDS; lane 0
-        // then adds them in order (one wave: its LDS accesses stay in order)
-        const int64_t q = base + threadIdx.x;
-        if (q < q1) {
-            tail[0][threadIdx.x] = sup[q];
-            tail[1][threadIdx.x] = sup[nsup + q];
-            tail[2][threadIdx.x] = sup[2 * nsup + q];
-        }
-        wave_sync();
-        if (threadIdx.x == 0) {
-            const int cnt = (q1 - base < 64) ? static_cast<int>(q1 - base) : 64;
-            for (int k = 0; k < cnt; ++k) {
-                sa = sa + tail[0][k];
-                sm = sm + tail[1][k];
-                sd = sd + tail[2][k];
-            }
-        }
-        wave_sync();
-    }
-    if (threadIdx.x != 0) return;
-    const float na = static_cast<float>(sqrt(sa));
-    const float nm = static_cast<float>(sqrt(sm));
-    const float nd = static_cast<float>(sqrt(sd));
-    const float num = k_eff * nm - na;
-    const float den = nd + eps;
+    const float norm = static_cast<float>(sqrt(sum));
+    const float na = __shfl(norm, 0), nm = __shfl(norm, 1), nd = __shfl(norm, 2);
+    if ((threadIdx.x & 63) != 0) return;
+    const float num = f.k_eff * nm - na;
+    const float den = nd + f.eps;
     const float pi_raw = num / den;
-    const float pi = (literal || pi_raw > 0.0f) ? pi_raw : 0.0f;
-    pi_seg[seg] = pi;
-    if (diag) {   // clamped elements (raw pi negative or NaN) and elements
-        const double size = static_cast<double>(seg_off[seg + 1] - seg_off[seg]);
-        if (!(pi_raw >= 0.0f)) atomicAdd(&diag[2], size);
-        atomicAdd(&diag[3], size);
+    const float pi = (f.literal || pi_raw > 0.0f) ? pi_raw : 0.0f;
+    f.pi_seg[seg] = pi;
+    if (f.diag) {   // clamped elements (raw pi negative or NaN) and elements
+        if (!(pi_raw >= 0.0f)) atomicAdd(&f.diag[2], static_cast<double>(size));
+        atomicAdd(&f.diag[3], static_cast<double>(size));
     }
     // Recording: every element of the segment takes this factor, so its
     // histogram entry is one bin holding the segment's size.
-    if (hist) {
-        uint32_t* row = hist + (hist_per_seg ? static_cast<int64_t>(seg) * GEM_PI_BINS : 0);
-        atomicAdd(&row[scale_bin(pi)], static_cast<uint32_t>(seg_off[seg + 1] - seg_off[seg]));
+    if (f.hist) {
+        uint32_t* row = f.hist + (f.hist_per_seg ? static_cast<int64_t>(seg) * GEM_PI_BINS : 0);
+        atomicAdd(&row[scale_bin(pi)], static_cast<uint32_t>(size));
     }
 }
 
-// The tree's upper levels and the factors: one block per (segment, aligned
-// block of kSegBlock indices) pair adds the 256 group sums of that index
-// block -- zero for groups outside the segment -- by the same adjacent-pairs
-// tree.  The last of a segment's pair blocks to finish (a device-scope
-// counter per segment, its sums released and acquired by device fences)
-// then reduces the segment's index-block sums and forms its factor; it also
-// resets the counter for the next launch.  Which block is last does not
-// change any sum: each is taken in one fixed order.
-__global__ __launch_bounds__(kBlock) void seg_blocks_kernel(const double* __restrict__ part,
-                                                            int64_t npart,
-                                                            const int64_t* __restrict__ part_off,
-                                                            const int64_t* __restrict__ seg_off,
-                                                            const int32_t* __restrict__ pair_seg,
-                                                            const int32_t* __restrict__ pair_blk,
-                                                            double* sup, int64_t nsup,
-                                                            const int64_t* __restrict__ sup_off,
-                                                            uint32_t* seg_done, SegFactors f)
+// The tree's upper levels and the factors.  A block has TEAMS times 256 threads
+// and takes up to TEAMS consecutive index blocks (of kSegBlock indices) of one
+// segment: a team of 256 threads adds an index block's 256 group sums -- zero for
+// groups outside the segment -- by the same adjacent-pairs tree.  A segment that
+// one block covers gets its factor there.  Else the blocks write their index
+// blocks' sums, and the last of them to finish (a device-scope counter per
+// segment, the sums released and acquired by device fences) adds the segment's
+// sums in order and forms the factor; it also resets the counter for the next
+// launch.  Which block is last does not change any sum: each is taken in one
+// fixed order.
+//
+// The launch is latency alone (a few hundred kilobytes are read): a chain of
+// dependent loads, the tree, the fences and the last block's loads.  With one
+// index block a thread block, its metadata found through four arrays and the
+// fences on every segment, it took 12.7 us a commit over 62 segments of 11.7M
+// parameters (70.3 us a commit in all, now 62.5; 161 segments of 1M: 26.7 and
+// 14.6).  So everything a block needs to know is one record (a unit), and four
+// index blocks to a thread block spare segments of up to a million indices the
+// fences.  Sixteen, four at a time, are slower than the fences (one segment of 3M
+// 26.6 us a commit, 23.6).
+template <int TEAMS>
+__global__ __launch_bounds__(TEAMS* kBlock) void seg_units_kernel(const double* __restrict__ part,
+                                                                  int64_t npart,
+                                                                  const SegUnit* __restrict__ units,
+                                                                  double* sup, int64_t nsup,
+                                                                  uint32_t* seg_done, SegFactors f)
 {
-    static_assert(kBlock * kSegGroup == kSegBlock, "one thread per group of an index block");
-    __shared__ double lds[3][4];
+    static_assert(kBlock * kSegGroup == kSegBlock, "256 threads for the groups of an index block");
+    static_assert(kWavesPerGroup == 4, "four waves per group");
+    __shared__ double lds[3][TEAMS * 4];
     __shared__ double tail[3][64];
     __shared__ int last;
-    const int32_t seg = pair_seg[blockIdx.x];
-    const int64_t blk = pair_blk[blockIdx.x];
-    const int64_t g_lo = seg_off[seg] / kSegGroup;
-    const int64_t g_hi = (seg_off[seg + 1] - 1) / kSegGroup;
-    const int64_t grp = blk * kBlock + threadIdx.x;
-    double va = 0.0, vm = 0.0, vd = 0.0;
-    if (grp >= g_lo && grp <= g_hi) {
-        // the group's four wave sums, (w0 + w1) + (w2 + w3)
-        static_assert(kWavesPerGroup == 4, "four waves per group");
-        const int64_t q = (part_off[seg] + (grp - g_lo)) * kWavesPerGroup;
-        const int64_t stride = npart * kWavesPerGroup;
-        const double* pa = part + q;
-        const double* pm = part + stride + q;
-        const double* pd = part + 2 * stride + q;
-        va = (pa[0] + pa[1]) + (pa[2] + pa[3]);
-        vm = (pm[0] + pm[1]) + (pm[2] + pm[3]);
-        vd = (pd[0] + pd[1]) + (pd[2] + pd[3]);
-    }
-    double sa = va, sm = vm, sd = vd;
-    block_tree_sum3(sa, sm, sd, lds);
-    if (threadIdx.x == 0) {
-        const int64_t q = sup_off[seg] + (blk - seg_off[seg] / kSegBlock);
-        sup[q] = sa;
-        sup[nsup + q] = sm;
-        sup[2 * nsup + q] = sd;
-        __threadfence();   // release this block's sums to every XCD
-        const uint32_t pairs = static_cast<uint32_t>(sup_off[seg + 1] - sup_off[seg]);
-        const uint32_t done = atomicAdd(&seg_done[seg], 1u) + 1u;
-        last = done == pairs;
-        if (done == pairs) atomicExch(&seg_done[seg], 0u);
+    const SegUnit u = units[blockIdx.x];
+    if (static_cast<int>(threadIdx.x >> 8) < u.nblk) {
+        const int64_t grp = (u.blk0 + (threadIdx.x >> 8)) * int64_t{kBlock} + (threadIdx.x & 255);
+        double va = 0.0, vm = 0.0, vd = 0.0;
+        if (grp >= u.g_lo && grp <= u.g_hi) {
+            // the group's four wave sums, (w0 + w1) + (w2 + w3)
+            const int64_t q = (u.part_first + (grp - u.g_lo)) * kWavesPerGroup;
+            const int64_t stride = npart * kWavesPerGroup;
+            const double* pa = part + q;
+            const double* pm = part + stride + q;
+            const double* pd = part + 2 * stride + q;
+            va = (pa[0] + pa[1]) + (pa[2] + pa[3]);
+            vm = (pm[0] + pm[1]) + (pm[2] + pm[3]);
+            vd = (pd[0] + pd[1]) + (pd[2] + pd[3]);
+        }
+        // the index block's sums: lane butterflies (which add pairs 2k, 2k+1, then
+        // pairs of pairs, ...) within each wave, then (wave 0 + wave 1) + (wave 2 + wave 3)
+#pragma unroll
+        for (int mask = 1; mask < 64; mask <<= 1) {
+            va = va + __shfl_xor(va, mask);
+            vm = vm + __shfl_xor(vm, mask);
+            vd = vd + __shfl_xor(vd, mask);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            lds[0][threadIdx.x >> 6] = va;
+            lds[1][threadIdx.x >> 6] = vm;
+            lds[2][threadIdx.x >> 6] = vd;
+        }
     }
     __syncthreads();
-    if (!last) return;
+    const int kind = threadIdx.x < 3 ? static_cast<int>(threadIdx.x) : 0;
+    auto pair_sum = [&](int p) {
+        const double* l = &lds[kind][4 * p];
+        return (l[0] + l[1]) + (l[2] + l[3]);
+    };
+    if (u.units == 1) {
+        if (threadIdx.x >= 64) return;
+        double sum = 0.0;
+        for (int p = 0; p < u.nblk; ++p) sum = sum + pair_sum(p);
+        segment_factor(u.seg, u.size, sum, f);
+        return;
+    }
+    if (threadIdx.x < 64) {
+        if (threadIdx.x < 3)
+            for (int p = 0; p < u.nblk; ++p) sup[kind * nsup + u.sup_at + p] = pair_sum(p);
+        if (threadIdx.x == 0) last = 0;
+        __threadfence();   // release this block's sums to every XCD
+        wave_sync();
+        if (threadIdx.x == 0) {
+            const uint32_t done = atomicAdd(&seg_done[u.seg], 1u) + 1u;
+            last = done == static_cast<uint32_t>(u.units);
+            if (last) atomicExch(&seg_done[u.seg], 0u);
+        }
+    }
+    __syncthreads();
+    if (!last || threadIdx.x >= 64) return;
     __threadfence();       // acquire the other blocks' sums
-    if (threadIdx.x < 64)
-        reduce_segment(seg, sup, nsup, sup_off, f.pi_seg, f.k_eff, f.eps, f.literal, seg_off,
-                       f.hist, f.hist_per_seg, f.diag, tail);
+    double sum = 0.0;
+    for (int64_t base = 0; base < u.sup_count; base += 64) {
+        // the lanes load 64 index blocks' sums of each kind at once; lanes 0 to
+        // 2 then add a kind each, in order (one wave: its LDS accesses stay in order)
+        const int64_t q = base + threadIdx.x;
+        if (q < u.sup_count) {
+            tail[0][threadIdx.x] = sup[u.sup_first + q];
+            tail[1][threadIdx.x] = sup[nsup + u.sup_first + q];
+            tail[2][threadIdx.x] = sup[2 * nsup + u.sup_first + q];
+        }
+        wave_sync();
+        const int cnt = (u.sup_count - base < 64) ? static_cast<int>(u.sup_count - base) : 64;
+        for (int k = 0; k < cnt; ++k) sum = sum + tail[kind][k];
+        wave_sync();
+    }
+    segment_factor(u.seg, u.size, sum, f);
 }
 
 template <bool BF16>
@@ -1839,16 +1833,20 @@ hipError_t launch_seg_step(const SegArgs& a, Source src, bool bf16_out, bool str
     return hipGetLastError();
 }
 
-hipError_t launch_seg_blocks(const double* part, int64_t npart, const int64_t* part_off,
-                             const int64_t* seg_off, const int32_t* pair_seg,
-                             const int32_t* pair_blk, int64_t npairs, double* sup,
-                             const int64_t* sup_off, uint32_t* seg_done, const SegFactors& f,
-                             hipStream_t stream)
+hipError_t launch_seg_units(const double* part, int64_t npart, const SegUnit* units,
+                            int64_t nunits, int teams, double* sup, int64_t nsup,
+                            uint32_t* seg_done, const SegFactors& f, hipStream_t stream)
 {
-    if (npairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(seg_blocks_kernel, dim3(static_cast<unsigned>(npairs)), dim3(kBlock), 0,
-                       stream, part, npart, part_off, seg_off, pair_seg, pair_blk, sup, npairs,
-                       sup_off, seg_done, f);
+    if (nunits <= 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(nunits));
+    if (teams == kSegTeams)
+        hipLaunchKernelGGL(seg_units_kernel<kSegTeams>, grid, dim3(kSegTeams * kBlock), 0, stream, part,
+                           npart, units, sup, nsup, seg_done, f);
+    else if (teams == 1)
+        hipLaunchKernelGGL(seg_units_kernel<1>, grid, dim3(kBlock), 0, stream, part, npart, units, sup,
+                           nsup, seg_done, f);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

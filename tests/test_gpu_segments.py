@@ -96,6 +96,26 @@ def test_partitions(G, kind, P):
     assert out[5].passes == T
 
 
+_B = 1 << 18   # indices of an index block; a thread block adds up four of them
+
+
+@pytest.mark.parametrize("seg", [
+    [0, 4 * _B, 4 * _B + 1, 9 * _B, 9 * _B + 700],              # 4, 1, 5 and 1 index blocks
+    [0, 1000, 8 * _B, 8 * _B + 5],                              # 8 blocks, two full units
+    [0, 17 * _B + 5],                                           # 18 blocks: five units
+    [0, _B, 2 * _B - 1, 6 * _B + 1],                            # 1, 1 and 6 blocks, edges off by one
+    [*range(0, 3000, 2), 6 * _B + 3000],                        # many segments: one block a unit
+], ids=["4-1-5-1", "8", "18", "off-by-one", "many"])
+def test_index_blocks_of_a_unit(G, seg):
+    n, T = 3, 5
+    seg = np.array(seg, dtype=np.int64)
+    P = int(seg[-1])
+    worker, tau = G.gem_schedule_make(n, T, G.GEM_LAW_EXP, seed=5)
+    print(f"[segments units] P={P} nseg={len(seg) - 1}", flush=True)
+    out, st = _run_both(G, P, n, worker, tau, _hp(G), seg)
+    _check(out, st, "units")
+
+
 def test_default_is_one_global_segment(G):
     P, n, T = 4099, 3, 30
     worker, tau = G.gem_schedule_make(n, T, G.GEM_LAW_EXP, seed=1)

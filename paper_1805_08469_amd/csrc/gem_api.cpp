@@ -319,36 +319,37 @@ struct RunShape {
     bool stream;    // non-temporal row accesses
 };
 
-// For a launch of k commits by `distinct` workers.  160 KiB of LDS per compute
-// unit hold 20 slots (40 with the shared moment's half slots), shared by the
-// blocks resident there; measured at 12.5M parameters, 988 commits:
+// Plans a launch of k commits by `distinct` workers into words.  160 KiB of LDS
+// per compute unit hold 20 slots (40 with the shared moment's half slots), shared
+// by the blocks resident there; measured at 12.5M parameters, 988 commits, unless
+// stated:
 //   - 4 blocks of 5 (10) slots when that holds every worker: nothing moves, and
 //     four waves per SIMD issue best (5 workers: 13.2 ms, 13.8 ms with 3 blocks,
 //     16.2 with 2);
-//   - then 3 blocks (10 workers: 15.6, 2 blocks 16.2; 64 workers
-//     equal; 100 workers 21.4, 2 blocks 21.2);
+//   - 3 blocks of 6 slots while fewer than 0.68 of the commits move their rows (10
+//     workers: 15.6, 2 blocks 16.2; 11.7M, 50 workers, 400 commits, 0.61: 6.90, 7.21;
+//     25M, 64 workers, 160 commits, 0.67: 6.43, 6.60);
 //   - beyond, 2 blocks of 10 slots: fewer rows move, and the rows in flight have
-//     larger shares of the Infinity Cache (150 workers: 21.7, 3 blocks 25.2; 300:
+//     larger shares of the Infinity Cache (25M, 100 workers, 160 commits, 0.72:
+//     6.93, 3 blocks 7.39; 990 commits, 0.71: 40.3, 41.2; 124M, 64 workers, 160
+//     commits of a Pareto schedule, 0.86: 35.0, 38.1; 150 workers: 21.7, 25.2; 300:
 //     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
-//     (300 workers: 17.2, 2 blocks 18.1);
-//   - from 61 workers on the same over 8M parameters or more, where the blocks are
-//     many rounds (124M parameters, 64 workers, 160 commits with bf16 updates: 37.6,
-//     3 blocks 40.7; 25M, 64 workers, 990 commits: 37.5, 38.4; 100 workers: 40.3,
-//     41.2); 4M with 100 workers keep 3 (400 commits: 2.77, 2 blocks 2.93).
+//     (300 workers: 17.2, 2 blocks 18.1).
 // Rows stream when few of them are found in the Infinity Cache again: beyond
 // 250 workers (300: 26.5 ms, default policy 27.2; 200: 24.5, 23.6), or when a
 // worker commits fewer than 1.4 times in the launch (25M parameters, 100
 // workers, 48 commits: 2.59 ms, 2.82; 96 commits: 4.91, 4.56).
-RunShape run_shape(const gem_handle* g, gemk::Variant v, int64_t k, int64_t distinct)
+RunShape plan_launch(const gem_handle* g, gemk::Variant v, const int32_t* worker, int k,
+                     int64_t distinct, uint32_t* words, int32_t* last)
 {
     const int all = static_cast<int>(std::min<int64_t>(g->lds_per_cu, 160 << 10)) / gemk::run_slot_bytes(v);
-    int blocks = 3;
-    if (distinct <= all / 4) blocks = 4;
-    else if (v != gemk::Variant::FastGlobal &&
-             (distinct > 100 || (distinct > 60 && g->Pp >= (int64_t{8} << 20))))
-        blocks = 2;
     RunShape r;
-    r.slots = std::min(std::max(all / blocks, gemk::kRunDepth), gemk::kRunMaxSlots);
+    auto plan = [&](int blocks) {
+        r.slots = std::min(std::max(all / blocks, gemk::kRunDepth), gemk::kRunMaxSlots);
+        return gemk::plan_run(worker, k, gemk::kRunDepth, r.slots, words, last);
+    };
+    if (distinct <= all / 4) plan(4);
+    else if (100 * plan(3) >= 68 * 2 * k && v != gemk::Variant::FastGlobal) plan(2);
     if (g->cache_policy != GEM_CACHE_AUTO) r.stream = g->cache_policy == GEM_CACHE_STREAM;
     else r.stream = stream_rows(g) && (distinct > 250 || 10 * k < 14 * distinct);
     return r;
@@ -418,10 +419,10 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
             last[w[j]] = 0;
         }
         for (int j = 0; j < k; ++j) last[w[j]] = -1;
-        const RunShape shape = run_shape(g, variant, k, distinct);
         const bool is_short = short_run(g, distinct, k, adaptive);
+        RunShape shape{};
         if (is_short) gemk::plan_short_run(w, k, a.sched, last.data());
-        else gemk::plan_run(w, k, gemk::kRunDepth, shape.slots, a.sched, last.data());
+        else shape = plan_launch(g, variant, w, k, distinct, a.sched, last.data());
         a.t0 = static_cast<uint32_t>(g->t);
         a.K = k;
         for (int j = 0; adaptive && j < k; ++j) {

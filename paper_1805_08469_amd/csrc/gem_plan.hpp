@@ -161,8 +161,9 @@ constexpr int kRunTauAt = kRunWords / 2;   // adaptive staleness: where the tau 
 // its end would be issued before its start is written); fewer than depth such
 // waits overlap, so one that may be dropped is always there.  words receives
 // the k schedule words and `depth` words that read no memory; last is scratch
-// of one int per worker (-1 on entry and on return).
-inline void plan_run(const int32_t* worker, int k, int depth, int slots, uint32_t* words, int32_t* last)
+// of one int per worker (-1 on entry and on return).  Returns the chunks read from
+// memory plus the chunks written to it.
+inline int plan_run(const int32_t* worker, int k, int depth, int slots, uint32_t* words, int32_t* last)
 {
     int next[kRunCommits], slot[kRunCommits];
     for (int j = k - 1; j >= 0; --j) {
@@ -198,11 +199,14 @@ inline void plan_run(const int32_t* worker, int k, int depth, int slots, uint32_
             holder[free_slot] = j;
         }
     }
+    int moved = 0;
     for (int j = 0; j < k; ++j) {
+        moved += ((words[j] & kRunSlotMask) == kRunMemory) + (slot[j] < 0);
         words[j] |= (slot[j] >= 0 ? static_cast<uint32_t>(slot[j]) : kRunMemory) << kRunDstShift;
         last[worker[j]] = -1;
     }
     for (int q = 0; q < depth; ++q) words[k + q] = 0u;
+    return moved;
 }
 
 // ---- runs over short vectors: every worker's rows in LDS ------------------------

@@ -62,7 +62,7 @@ int replay(const std::vector<int32_t>& w, int n, int depth, int slots)
     const int k = static_cast<int>(w.size());
     std::vector<uint32_t> words(k + depth, 0xFFFFFFFFu);
     std::vector<int32_t> last(n, -1);
-    plan_run(w.data(), k, depth, slots, words.data(), last.data());
+    const int planned = plan_run(w.data(), k, depth, slots, words.data(), last.data());
     for (int v : last)
         if (v != -1) fail("scratch not restored", 0, k, slots);
     std::vector<int> mem(n, 0), cur(n, 0);
@@ -97,6 +97,11 @@ int replay(const std::vector<int32_t>& w, int n, int depth, int slots)
         }
         fetch(j % depth, words[j + depth]);
     }
+    int moved = 0;
+    for (int j = 0; j < k; ++j)
+        moved += ((words[j] & kRunSlotMask) == kRunMemory) +
+                 (((words[j] >> kRunDstShift) & kRunSlotMask) == kRunMemory);
+    if (moved != planned) fail("moved chunks", moved, k, slots);
     for (int x = 0; x < n; ++x)
         if (mem[x] != cur[x]) fail("memory behind after the run", x, k, slots);
     return held;

@@ -634,7 +634,7 @@ int run_segments(gem_handle* g, const int32_t* worker, int64_t T, Source src,
         f.hist = nullptr;
         if (g->hist_on && g->hist_count < g->hist_cap)
             f.hist = g->pi_hist + g->hist_count * g->hist_rows * GEM_PI_BINS;
-        GEM_HIP(gemk::launch_seg_units(g->part, g->npart, g->units, g->nunits, g->seg_teams, g->sup,
+        GEM_HIP(gemk::launch_seg_blocks(g->part, g->npart, g->units, g->nunits, g->seg_teams, g->sup,
                                        g->nsup, g->seg_done, f, g->stream));
         if (g->hist_on) g->hist_count += 1;
         if (g->diag_on) g->diag_commits += 1;

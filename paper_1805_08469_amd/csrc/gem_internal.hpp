@@ -95,7 +95,7 @@ static_assert(sizeof(RunArgs) <= 4096, "the argument block fits");
 // Segment-norm scale factors.  A sum of squares is the adjacent-pairs tree
 // over aligned blocks of kSegBlock indices, then the blocks in order.  The
 // step kernel forms the tree's lower levels, one aligned group of
-// kSegGroup = 4 * 256 indices per thread block; seg_units_kernel the upper
+// kSegGroup = 4 * 256 indices per thread block; seg_blocks_kernel the upper
 // levels, 256 groups per index block.
 constexpr int64_t kSegGroup = 1024;
 constexpr int64_t kSegBlock = 1 << 18;
@@ -186,7 +186,7 @@ struct SegFactors {
     uint32_t* hist;       // this commit's histogram rows, or null
     double* diag;         // [4] accumulators, or null
 };
-// The part of a segment that one block of seg_units_kernel adds up: up to
+// The part of a segment that one block of seg_blocks_kernel adds up: up to
 // `teams` consecutive index blocks (kSegBlock indices each) of it.
 struct SegUnit {
     int64_t part_first;   // the segment's first slot of group sums
@@ -206,7 +206,7 @@ struct SegUnit {
 constexpr int kSegTeams = 4;
 constexpr int64_t kSegUnitMost = 1024;
 // seg_done: [nseg] counters, zero between launches (each launch leaves them zero).
-hipError_t launch_seg_units(const double* part, int64_t npart, const SegUnit* units,
+hipError_t launch_seg_blocks(const double* part, int64_t npart, const SegUnit* units,
                             int64_t nunits, int teams, double* sup, int64_t nsup,
                             uint32_t* seg_done, const SegFactors& f, hipStream_t stream);
 hipError_t launch_generate(const float* S, int64_t nw, int32_t w, const float* h,

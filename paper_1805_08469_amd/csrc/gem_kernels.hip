@@ -1113,7 +1113,7 @@ __global__ __launch_bounds__(kBlock) void short_run_kernel(const RunArgs a)
 // A commit's pi needs sums of squares over whole segments, so each commit is
 // split in two launches: the step kernel starts commit t (forms d, m and the
 // drift, stores m, writes each 1024-index group's tree sums of squares), and
-// seg_units_kernel adds the group sums of each 2^18-index block by the same
+// seg_blocks_kernel adds the group sums of each 2^18-index block by the same
 // tree, after which the last block of each segment adds the block sums in
 // order and forms the segment's pi.  The next step kernel applies those
 // factors (and the pull) before starting the next commit, generating the
@@ -1323,7 +1323,7 @@ void seg_step_kernel(const SegArgs a)
             cd = (xd[0] + xd[1]) + (xd[2] + xd[3]);
         }
         // The wave's 256-index subtree (lane butterflies add pairs 2k, 2k+1,
-        // then pairs of pairs, ...); seg_units_kernel adds the group's four
+        // then pairs of pairs, ...); seg_blocks_kernel adds the group's four
         // wave sums as (w0 + w1) + (w2 + w3), the next level of the same
         // tree.  No barrier: each wave writes its own slot.
 #pragma unroll
@@ -1399,7 +1399,7 @@ __device__ void segment_factor(int32_t seg, int64_t size, double sum, const SegF
 // fences.  Sixteen, four at a time, are slower than the fences (one segment of 3M
 // 26.6 us a commit, 23.6).
 template <int TEAMS>
-__global__ __launch_bounds__(TEAMS* kBlock) void seg_units_kernel(const double* __restrict__ part,
+__global__ __launch_bounds__(TEAMS* kBlock) void seg_blocks_kernel(const double* __restrict__ part,
                                                                   int64_t npart,
                                                                   const SegUnit* __restrict__ units,
                                                                   double* sup, int64_t nsup,
@@ -1833,17 +1833,17 @@ hipError_t launch_seg_step(const SegArgs& a, Source src, bool bf16_out, bool str
     return hipGetLastError();
 }
 
-hipError_t launch_seg_units(const double* part, int64_t npart, const SegUnit* units,
+hipError_t launch_seg_blocks(const double* part, int64_t npart, const SegUnit* units,
                             int64_t nunits, int teams, double* sup, int64_t nsup,
                             uint32_t* seg_done, const SegFactors& f, hipStream_t stream)
 {
     if (nunits <= 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(nunits));
     if (teams == kSegTeams)
-        hipLaunchKernelGGL(seg_units_kernel<kSegTeams>, grid, dim3(kSegTeams * kBlock), 0, stream, part,
+        hipLaunchKernelGGL(seg_blocks_kernel<kSegTeams>, grid, dim3(kSegTeams * kBlock), 0, stream, part,
                            npart, units, sup, nsup, seg_done, f);
     else if (teams == 1)
-        hipLaunchKernelGGL(seg_units_kernel<1>, grid, dim3(kBlock), 0, stream, part, npart, units, sup,
+        hipLaunchKernelGGL(seg_blocks_kernel<1>, grid, dim3(kBlock), 0, stream, part, npart, units, sup,
                            nsup, seg_done, f);
     else
         return hipErrorInvalidValue;

@@ -416,6 +416,10 @@ def main() -> int:
         "roofline": {
             **roof,
             "alg_bytes_per_launch": alg_per_pass,
+            # A run's launches take many passes' commits and keep rows on the chip:
+            # they move fewer bytes than the passes of K commits counted here, and
+            # the algorithmic rate can exceed the memory's.
+            "alg_bytes_counted": "passes of at most K commits",
             "avg_launch_ms": avg_pass_s * 1e3,
             "kernel": (("seg_step_kernel + seg_blocks_kernel" + (", streaming" if streaming else ""))
                        if args.pi_scope == "segment"

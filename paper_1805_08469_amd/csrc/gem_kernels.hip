@@ -882,11 +882,14 @@ __device__ __forceinline__ void put_row_at(float* base, bool mem, uint32_t byte_
 //   - theta, h and theta* are read once per run instead of once per pass;
 //   - the rows a block moves again lie in the Infinity Cache's share of the
 //     few hundred blocks in flight, if the workers are not too many.
-// What is left is 220 VALU instructions per wave and commit, issued at 0.43 ms
-// per 32 commits and 12.5M elements when all rows stay in LDS, and the rows'
-// traffic at 6.5 TB/s between L2 and the fabric, the rate a copy reaches (100
-// workers: 0.69 ms for 4.5 GB).  Measured at 25M parameters and 100 workers,
-// 988 commits: 55.3 ms in passes of 32, 39.8 ms here.
+// What is left is 197 VALU instructions per wave and commit (203 with bf16
+// updates), one per SIMD every four cycles when all rows stay in LDS, and the rows'
+// traffic between L2 and the fabric at 6.0-6.6 TB/s, the rate a copy reaches.
+// Measured at 25M parameters and 100 workers, 1000 commits: 56.4 ms in passes of
+// 32, 40.8 ms here; with the shared moment 40.7 and 31.5 (VALU issue at 0.99).
+//
+// Two elements a thread, a lane pair sharing a Philox block, would give each
+// element twice the slots: 221 instructions, and within 2% at every size.
 //
 // Rows come DEPTH commits ahead into a register ring; 3 measured best (2 and 4
 // are 2% and 1% slower, 6 and 8 more).  Noise is drawn one commit ahead, in

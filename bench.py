@@ -151,23 +151,24 @@ def copy_ceiling(G, torch, nbytes: int, reps: int = 10) -> float:
     return 2 * nbytes / (ms * 1e-3) / 1e9
 
 
-def compute_floor(G, torch, wl, hp, cache: int, pi_hist: bool, passes: int = 12) -> float:
-    """Milliseconds of compute per commit of the workload's pass kernel: the
-    same kernel over the same P with one worker, in passes of GEM_K_MAX
-    commits.  That worker's snapshot and moment stay in the register slots for
-    the whole pass, so a pass moves 32 bytes per parameter for 32 commits and
-    its time is the noise generator's and the commit arithmetic's.  A real
-    configuration of the method (GEM with a single worker), run through
-    gem_sim_run."""
+def compute_floor(G, torch, wl, hp, cache: int, pi_hist: bool) -> float:
+    """Milliseconds of compute per commit of the workload's kernel: the same
+    kernel over the same P with two workers in turn (when recording, with one).
+    Their snapshots and moments stay on the chip for the whole launch, so its
+    time is the noise generator's and the commit arithmetic's.  (One worker
+    alone waits on its own rows: each of its commits starts from the last one's
+    result.)  A real configuration of the method, run through gem_sim_run; over
+    a short vector with as many commits as keep a launch's start a small part."""
     import numpy as np
     stream = torch.cuda.current_stream()
     K = G.GEM_K_MAX
-    T = passes * K
-    worker = np.zeros(T, dtype=np.int32)
-    with G.Gem(wl.P, 1, hp, stream=stream.cuda_stream) as g:
+    T = (62 if wl.P < 1 << 20 else 12) * K
+    workers = 1 if pi_hist else 2
+    worker = np.arange(T, dtype=np.int32) % workers
+    with G.Gem(wl.P, workers, hp, stream=stream.cuda_stream) as g:
         g.set_cache_policy(cache)
         g.set_quadratic(*problem_arrays(wl), wl.lr, wl.sigma, wl.seed, bf16=wl.bf16)
-        g.sim_run(worker[:2 * K], None, K)                  # warm-up
+        g.sim_run(worker if wl.P < 1 << 20 else worker[:2 * K], None, K)    # warm-up
         if pi_hist:
             G.gem_pi_hist_start(g.h, T)
         torch.cuda.synchronize()

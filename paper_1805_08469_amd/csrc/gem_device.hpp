@@ -128,21 +128,25 @@ __device__ __forceinline__ float div_rn_core(float a, float b)
 __device__ float mul_legacy(float a, float b) __asm("llvm.amdgcn.fmul.legacy");
 
 // sqrt(x), correctly rounded, for the Box-Muller radicands x = -2 ln(k 2^-24),
-// k in [1, 2^24] (+0 or in [1.1e-7, 33.3]).  One Newton step from the hardware
+// k in [1, 2^24] (zero or in [1.1e-7, 33.3]).  One Newton step from the hardware
 // reciprocal root y: g = x y, then g + (x - g^2) (y / 2).  The step is the
 // correctly rounded root for every one of the 2^24 radicands (the self-test
 // library checks all of them on the device).  Five instructions and the root;
 // stepping v_sqrt's result to the neighbour with the right residual sign takes
-// eight.  x = 0 has y = inf; the legacy product, whose zero times anything is
-// zero, makes g = 0 and the correction 0 * 2^127.  y / 2 is an integer step of
-// the exponent.
+// eight.  y / 2 is an integer step of the exponent.
+//
+// The radicand of k = 2^24 is defined as -2 ln 1 = -0, whose root is -0; here it
+// arrives as +0 (radicand_of_k24).  Its y is inf and the legacy product, whose
+// zero times anything is +0, gives +0.  The step is therefore taken with both
+// signs turned, n = -g and -(x - g^2) = n^2 - x, which changes no bit of any
+// other root and ends here in (-0) 2^127 + (-0) = -0.
 __device__ __forceinline__ float radicand_root(float x)
 {
     const float y = __builtin_amdgcn_rsqf(x);
-    const float g = mul_legacy(x, y);
+    const float n = mul_legacy(x, -y);
     const float half_y = __uint_as_float(__float_as_uint(y) - 0x00800000u);
-    const float e = __builtin_fmaf(-g, g, x);
-    return __builtin_fmaf(e, half_y, g);
+    const float e = __builtin_fmaf(n, n, -x);
+    return __builtin_fmaf(-e, half_y, -n);
 }
 
 // num / den, correctly rounded for every input: the core steps when both
@@ -188,7 +192,8 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 // -4 (f - 1), exact), s'^2 = 16 s^2 against coefficients divided by 16 per
 // degree, and the tail and head times -2.  Scaling by a power of two commutes
 // with rounding (nothing here is subnormal or overflows), so the bits are
-// those of the defined steps, in 2 instructions fewer.
+// those of the defined steps, in 2 instructions fewer; but for k = 2^24, whose
+// defined radicand is -0 and which is +0 here (radicand_root restores the sign).
 //
 // The reduction works on the integer: k as binary32 (exact) has u's
 // significand and an exponent 24 larger; subtracting the bits of 2^24 * the
@@ -227,7 +232,8 @@ __device__ __forceinline__ float radicand_of_k24(uint32_t k)
 // Quadrant q (bits 30 and 31 of xb + 2^29): (sin, cos) = (sx, cx), (cx, -sx),
 // (-sx, -cx), (-cx, sx): an odd quadrant takes (cx, -sx), and quadrants 2 and
 // 3 negate both, which here goes into r's sign before the two products (a
-// product's bits but for its sign do not depend on its factors' signs).
+// product's bits but for its sign do not depend on its factors' signs).  r may
+// be of either sign, zeros included: the radius of u1 = 1 is -0.
 __device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, float& zs)
 {
     const int rem = static_cast<int>(xb << 2) >> 10;

@@ -108,9 +108,9 @@ __global__ __launch_bounds__(kThreads) void radius_kernel(unsigned long long* ba
     const uint32_t k = blockIdx.x * kThreads + threadIdx.x + 1u;   // 1 .. 2^24
     const float want = -2.0f * defined_ln(static_cast<float>(k) * 0x1p-24f);
     const float x = gemk::radicand_of_k24(k);
-    // (-2 ln 1 is -0 in the defined steps and +0 here: equal, and so are the roots)
-    if (!(x == want)) atomicAdd(bad, 1ull);
-    if (!(gemk::radicand_root(x) == __builtin_sqrtf(want))) atomicAdd(bad, 1ull);
+    // the radicand of u = 1 is -0 as defined and arrives as +0; the root is -0
+    if (!same_bits(x, k == (1u << 24) ? 0.0f : want)) atomicAdd(bad, 1ull);
+    if (!same_bits(gemk::radicand_root(x), __builtin_sqrtf(want))) atomicAdd(bad, 1ull);
 }
 
 __global__ __launch_bounds__(kThreads) void turn_kernel(float r, unsigned long long* bad)

@@ -69,3 +69,46 @@ def test_generate_bit_exact(torch_cuda, P, bf16):
     if bf16:
         ref = O.round_bf16(ref)
     assert_parity("dtheta", d, ref)
+
+
+# (seed, index) whose noise at clock 0 has u1 = 1, the first of the pair: the
+# radius sqrt(-2 ln 1) is -0 and both normals are zeros whose signs it turns.
+U1_IS_ONE = [(5947, 166), (13045, 138), (96227, 34)]
+
+
+def _bits(a):
+    return np.ascontiguousarray(a, dtype=np.float32).view(np.uint32)
+
+
+@pytest.mark.parametrize("seed,index", U1_IS_ONE)
+def test_signs_of_zero_normals(torch_cuda, seed, index):
+    """With h = 0 and s < theta*, h (s - theta*) is -0 and the sign of a zero
+    normal is that of the generated update; with a negative momentum it is that
+    of the worker's moment too, in each kernel that draws noise (one pass, the
+    short-vector kernel, the run kernel)."""
+    from paper_1805_08469_amd import gem as G
+    torch = torch_cuda
+    lr, sigma, n = 0.01, 0.1, 2
+    pair = [index, index + 1]
+    xi = O.normals(seed, 0, 0, 256)
+    assert np.all(xi[pair] == 0) and np.any(np.signbit(xi[pair]))
+    hp = G.gem_hyperparams_default()
+    hp.momentum = -0.9
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for P, T in ((256, 1), (256, 2), (64 * 8 * cus + 1029, 2)):
+        h, ts = np.zeros(P, np.float32), np.ones(P, np.float32)
+        worker = np.arange(T, dtype=np.int32) % n
+        with G.Gem(P, n, hp) as g:
+            g.set_quadratic(h, ts, lr, sigma, seed)
+            for dtype in (G.GEM_F32, G.GEM_BF16):
+                d = _gen(torch, g, P, 0, dtype)[:256]
+                ref = (np.float32(-lr) * fma32(h[:256], -ts[:256], np.float32(sigma) * xi)).astype(np.float32)
+                if dtype == G.GEM_BF16:
+                    ref = O.round_bf16(ref)
+                assert np.array_equal(_bits(d), _bits(ref)), dtype
+            g.sim_run(worker, None, 1)
+            m = g.state(0, G.GEM_MOMENT)[:256]
+        st = O.State.initial(n, 256)
+        O.run(O.Hyper(lr=lr, sigma=sigma, momentum=-0.9, seed=seed), P, st, np.arange(256), h[:256],
+              ts[:256], worker, None)
+        assert np.array_equal(_bits(m), _bits(st.M[0])), f"P={P} T={T}"

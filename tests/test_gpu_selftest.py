@@ -55,7 +55,7 @@ def test_box_muller_radius_exhaustive(lib):
     assert _count(lib.gem_selftest_radius) == 0
 
 
-@pytest.mark.parametrize("r", [1.0, 1.2345678, 5.7681, 1e-3, 0.0])
+@pytest.mark.parametrize("r", [1.0, 1.2345678, -5.7681, 1e-3, 0.0, -0.0])
 def test_angle_products_exhaustive(lib, r):
     """r cos(phi) and r sin(phi) of every angle against the defined steps."""
     assert _count(lib.gem_selftest_turn, r) == 0

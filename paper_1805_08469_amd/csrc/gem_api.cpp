@@ -294,8 +294,8 @@ int run_passes(gem_handle* g, const std::vector<Pass>& passes, Source src,
         // variant.
         const bool rec = hist && !g->diag_on && g->hist_rows == 1 && src == Source::Generated &&
                          variant == gemk::Variant::Fast;
-        // a recording pass loops 8 blocks per compute unit over the groups
-        a.rec_grid = rec ? 8 * g->cus : 0;
+        // a recording pass loops its blocks over the groups
+        a.rec_grid = rec ? gemk::rec_blocks((g->Pp + 1023) / 1024, g->cus) : 0;
         const bool diag = (g->diag_on || hist) && !rec;
         // a single-commit pass runs the kernel compiled for one commit
         const int d = p.K == 1 && !diag && !rec ? gemk::kPrefetchNone : depth;

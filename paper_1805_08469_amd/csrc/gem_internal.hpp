@@ -43,7 +43,7 @@ struct PassArgs {
     const int64_t* hseg_off; // [hist_rows + 1] segment offsets (per-segment mode)
     const int32_t* hseg_grp; // [groups] segment of each 1024-element group's first element
     int32_t hist_rows;
-    int32_t rec_grid;        // blocks of a recording pass (0: one per group of 1024 elements)
+    int32_t rec_grid;        // blocks of a recording pass (rec_blocks)
     float* sink_S;           // [kSinkChunks * 4] target of loads/stores a step does not need
     float* sink_M;
     int64_t sink_mask;       // kSinkChunks - 1

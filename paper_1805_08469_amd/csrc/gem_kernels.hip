@@ -62,9 +62,9 @@ constexpr int kBlock = 256;
 constexpr int kHistLdsSegs = 8;
 
 // Recording pass (REC): the block keeps one histogram per commit of the pass
-// in LDS for the whole pass, two bins per 32-bit word (16-bit counts: a block
-// counts at most 1024 elements per commit), cleared once before the pass and
-// flushed once after it -- no barrier between commits.
+// in LDS for the whole pass, two bins per 32-bit word (16-bit counts: the grid
+// gives a block at most kRecGroups groups of 1024 elements), cleared once before
+// the pass and flushed once after it -- no barrier between commits.
 constexpr int kRecWords = (GEM_PI_BINS + 1) / 2;
 
 struct DiagAcc {
@@ -731,7 +731,7 @@ __device__ __forceinline__ void pass_group(const PassArgs& a, int64_t grp, uint3
 }
 
 // The fused pass: one group per block; the recording variant (REC) loops its
-// blocks over the groups (a grid of a.rec_grid blocks, 0 for one per group)
+// blocks over the groups (a grid of a.rec_grid blocks)
 // so that each block's per-pass LDS histograms gather many groups before
 // their single flush -- one global atomic per nonzero bin and block.
 template <Source SRC, Variant V, bool BF16, bool DIAG, int DEPTH, bool NT, bool REC>
@@ -1639,9 +1639,8 @@ hipError_t launch_one(const PassArgs& a, hipStream_t st, uint32_t lds = 0)
     }
     static_assert(DEPTH > 1 || (!REC && !DIAG), "depth 1: the plain single-commit pass");
     if (DEPTH == 1 && a.K != 1) return hipErrorInvalidValue;
-    unsigned grid = blocks_for(a.Pp >> 2);
-    if (REC && a.rec_grid > 0 && static_cast<unsigned>(a.rec_grid) < grid)
-        grid = static_cast<unsigned>(a.rec_grid);
+    if (REC && a.rec_grid < 1) return hipErrorInvalidValue;
+    const unsigned grid = REC ? static_cast<unsigned>(a.rec_grid) : blocks_for(a.Pp >> 2);
     hipLaunchKernelGGL((pass_kernel<SRC, V, BF16, DIAG, DEPTH, NT, REC>), dim3(grid), dim3(kBlock),
                        lds, st, a);
     return hipGetLastError();

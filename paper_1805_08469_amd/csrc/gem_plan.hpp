@@ -41,6 +41,19 @@ inline uint32_t deep_lds_bytes(int64_t lds_per_cu)
     return (b + slack) * kDeepBlocksPerCU <= lds_per_cu ? static_cast<uint32_t>(b) : 0u;
 }
 
+// Blocks of a recording pass over `groups` groups of 1024 elements: 8 a compute
+// unit (one per group if their number, cus, is 0: unknown), but as many as
+// leave no block more than kRecGroups groups, whose elements a block's 16-bit
+// counts hold even when all of a commit's factors fall into one bin.
+constexpr int64_t kRecGroups = 63;
+inline int32_t rec_blocks(int64_t groups, int cus)
+{
+    const int64_t least = (groups + kRecGroups - 1) / kRecGroups;
+    const int64_t most = cus > 0 ? int64_t{8} * cus : groups;
+    const int64_t blocks = most > least ? most : least;
+    return static_cast<int32_t>(blocks < groups ? blocks : groups);
+}
+
 constexpr uint32_t kRouteSlotMask = 0xFu;
 constexpr uint32_t kRouteDstShift = 4;
 constexpr uint32_t kFromRing = 0xFu;

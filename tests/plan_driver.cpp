@@ -182,6 +182,16 @@ int main(int argc, char** argv)
               b * (gemk::kDeepBlocksPerCU + 1) > lds))
             fail("LDS reservation does not cap the deep pass", 0, static_cast<int>(lds >> 10));
     }
+    // A recording pass's blocks: no more than groups, and no block takes more
+    // groups than its 16-bit counts hold (64 x 1024 do not fit).
+    static_assert(gemk::kRecGroups * 1024 <= 65535, "16-bit counts");
+    for (int cus : {0, 1, 104, 256})
+        for (int64_t groups : {1, 2, 63, 64, 2047, 2048, 2049, 129024, 129025, 131072, 131073, 2097152}) {
+            const int64_t b = gemk::rec_blocks(groups, cus);
+            if (b < 1 || b > groups || (groups + b - 1) / b > gemk::kRecGroups ||
+                (groups <= int64_t{8} * cus && b != groups))
+                fail("blocks of a recording pass", cus, static_cast<int>(groups));
+        }
     if (gemk::deep_lds_bytes(0) != 0 || gemk::deep_lds_bytes(2048) != 0)
         fail("LDS reservation on a CU without room for it", 0, 0);
     std::printf("passes %ld (lower bound %ld) commits %ld row reads %ld writes %ld distinct %ld\n",

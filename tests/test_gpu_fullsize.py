@@ -51,6 +51,29 @@ def _free_bytes():
     return free
 
 
+def test_recording_past_16_bit_counts(G):
+    """A recording pass's blocks count in 16 bits and loop over groups of 1024
+    elements; over this vector 8 blocks a compute unit would take up to 65 groups
+    each.  Without noise the first commit's factors are all 1, and a second
+    worker that sends the same update has all of its clamped: two bins that
+    hold every element."""
+    import torch
+    P = (64 * 8 * torch.cuda.get_device_properties(0).multi_processor_count + 200) * 1024 - 3
+    if _free_bytes() < 4 * P * 8:
+        pytest.skip("not enough device memory")
+    one = np.ones(P, dtype=np.float32)
+    print(f"[recording] P={P}", flush=True)
+    with G.Gem(P, 2) as g:
+        g.set_quadratic(one, one, 0.01, 0.0, 1)
+        G.gem_pi_hist_start(g.h, 2)
+        g.sim_run(np.array([0, 1], np.int32), None, 2)
+        hist = G.gem_pi_hist_read(g.h, 2)
+    want = np.zeros((2, G.GEM_PI_BINS), dtype=np.int64)
+    want[0, 2 + 16 * 20] = P      # factor 1 = 2^0
+    want[1, 0] = P                # clamped
+    assert np.array_equal(hist.astype(np.int64), want)
+
+
 def _workload_parity(G, name, T=None, proxy=0):
     from paper_1805_08469_amd.workloads import WORKLOADS, problem
     wl = WORKLOADS[name]

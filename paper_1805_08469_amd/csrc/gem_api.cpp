@@ -313,63 +313,15 @@ int run_passes(gem_handle* g, const std::vector<Pass>& passes, Source src,
     return GEM_OK;
 }
 
-// How a run's launch shares the compute units and reads its rows.
-struct RunShape {
-    int slots;      // LDS slots of a block
-    bool stream;    // non-temporal row accesses
-};
-
-// Plans a launch of k commits by `distinct` workers into words.  160 KiB of LDS
-// per compute unit hold 20 slots (40 with the shared moment's half slots), shared
-// by the blocks resident there; measured at 12.5M parameters, 988 commits, unless
-// stated:
-//   - 4 blocks of 5 (10) slots when that holds every worker: nothing moves, and
-//     four waves per SIMD issue best (5 workers: 13.2 ms, 13.8 ms with 3 blocks,
-//     16.2 with 2);
-//   - 3 blocks of 6 slots while fewer than 0.68 of the commits move their rows (10
-//     workers: 15.6, 2 blocks 16.2; 11.7M, 50 workers, 400 commits, 0.61: 6.90, 7.21;
-//     25M, 64 workers, 160 commits, 0.67: 6.43, 6.60);
-//   - beyond, 2 blocks of 10 slots: fewer rows move, and the rows in flight have
-//     larger shares of the Infinity Cache (25M, 100 workers, 160 commits, 0.72:
-//     6.93, 3 blocks 7.39; 990 commits, 0.71: 40.3, 41.2; 124M, 64 workers, 160
-//     commits of a Pareto schedule, 0.86: 35.0, 38.1; 150 workers: 21.7, 25.2; 300:
-//     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
-//     (300 workers: 17.2, 2 blocks 18.1).
-// Rows stream when few of them are found in the Infinity Cache again: beyond
-// 250 workers (300: 26.5 ms, default policy 27.2; 200: 24.5, 23.6), or when a
-// worker commits fewer than 1.4 times in the launch (25M parameters, 100
-// workers, 48 commits: 2.59 ms, 2.82; 96 commits: 4.91, 4.56).
-RunShape plan_launch(const gem_handle* g, gemk::Variant v, const int32_t* worker, int k,
-                     int64_t distinct, uint32_t* words, int32_t* last)
+// Whether run_kernel's row accesses are non-temporal.  Rows stream when few of
+// them are found in the Infinity Cache again: beyond 250 workers (12.5M
+// parameters, 988 commits, 300 workers: 26.5 ms, default policy 27.2; 200: 24.5,
+// 23.6), or when a worker commits fewer than 1.4 times in the launch (25M
+// parameters, 100 workers, 48 commits: 2.59 ms, 2.82; 96 commits: 4.91, 4.56).
+bool stream_run(const gem_handle* g, int k, int64_t distinct)
 {
-    const int all = static_cast<int>(std::min<int64_t>(g->lds_per_cu, 160 << 10)) / gemk::run_slot_bytes(v);
-    RunShape r;
-    auto plan = [&](int blocks) {
-        r.slots = std::min(std::max(all / blocks, gemk::kRunDepth), gemk::kRunMaxSlots);
-        return gemk::plan_run(worker, k, gemk::kRunDepth, r.slots, words, last);
-    };
-    if (distinct <= all / 4) plan(4);
-    else if (100 * plan(3) >= 68 * 2 * k && v != gemk::Variant::FastGlobal) plan(2);
-    if (g->cache_policy != GEM_CACHE_AUTO) r.stream = g->cache_policy == GEM_CACHE_STREAM;
-    else r.stream = stream_rows(g) && (distinct > 250 || 10 * k < 14 * distinct);
-    return r;
-}
-
-// Whether a launch of k commits by `distinct` workers goes to the short-vector
-// kernel, which holds all their rows in LDS.  It takes 0.12 us a commit for as
-// many blocks as are resident, up to 8 a compute unit with 20 workers and 2 with
-// 100; run_kernel takes 0.5 up to 262144 elements.  Past twice the resident blocks
-// or 8 a compute unit the latter's fewer instructions per element win.  Measured
-// (400 commits and the reads after them, short and run kernel, us): 20 workers,
-// 65536 elements 199 and 342, 131072: 257 and 345, 262144: 341 and 351, 524288:
-// 522 and 438; 100 workers, 32768: 192 and 343, 65536: 261 and 343, 131072: 386 and
-// 347; kappa = 2, 131072: 255 and 421.
-bool short_run(const gem_handle* g, int64_t distinct, int k, bool adaptive)
-{
-    if (distinct > gemk::kShortSlots) return false;
-    const int64_t lds = gemk::short_run_lds(static_cast<int>(distinct), k, adaptive);
-    const int64_t per_cu = (g->Pp / gemk::kShortElems + g->cus - 1) / g->cus;
-    return per_cu <= std::min<int64_t>(8, 2 * (g->lds_per_cu / lds));
+    if (g->cache_policy != GEM_CACHE_AUTO) return g->cache_policy == GEM_CACHE_STREAM;
+    return stream_rows(g) && (distinct > 250 || 10 * k < 14 * distinct);
 }
 
 // Queue a run of T commits on generated updates as launches of up to
@@ -396,12 +348,8 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
     // (the general variant takes an eps of any size)
     const gemk::Variant variant = g->hp.eps < 0x1p-60f ? gemk::Variant::General : kernel_variant(g->hp);
     const bool adaptive = g->hp.rule == GEM_RULE_ADAPTIVE;
-    // The commits of one launch: as many as the argument block takes, and at
-    // most 2^36 element-commits (a tenth of a second), so that a launch over a
-    // very large vector does not keep the GPU from other streams for long.
-    const int64_t most = std::min<int64_t>(
-        adaptive ? gemk::kRunTauAt - gemk::kRunDepth : gemk::kRunCommits,
-        std::max<int64_t>(GEM_K_MAX, (int64_t{1} << 36) / g->Pp));
+    const gemk::RunTarget to{g->Pp, g->cus, g->lds_per_cu, gemk::run_slot_bytes(variant), adaptive};
+    const int64_t most = gemk::run_commits(to);
     const int64_t launches = (T + most - 1) / most;
     const size_t n = static_cast<size_t>(g->n);
     std::vector<int32_t> last(n, -1);
@@ -413,16 +361,7 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
     for (int64_t l = 0; l < launches; ++l) {
         const int k = static_cast<int>((T - j0) / (launches - l));   // launches of even length
         const int32_t* w = worker + j0;
-        int64_t distinct = 0;
-        for (int j = 0; j < k; ++j) {
-            distinct += last[w[j]] < 0;
-            last[w[j]] = 0;
-        }
-        for (int j = 0; j < k; ++j) last[w[j]] = -1;
-        const bool is_short = short_run(g, distinct, k, adaptive);
-        RunShape shape{};
-        if (is_short) gemk::plan_short_run(w, k, a.sched, last.data());
-        else shape = plan_launch(g, variant, w, k, distinct, a.sched, last.data());
+        const gemk::RunLaunch p = gemk::plan_launch(to, w, k, a.sched, last.data());
         a.t0 = static_cast<uint32_t>(g->t);
         a.K = k;
         for (int j = 0; adaptive && j < k; ++j) {
@@ -430,10 +369,9 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
             pull[w[j]] = next_pull(g, g->t + j);
         }
         const bool bf16 = g->sp.update_dtype == GEM_BF16;
-        if (is_short) GEM_HIP(gemk::launch_short_run(a, variant, bf16, g->stream));
-        else GEM_HIP(gemk::launch_run(a, variant, bf16, shape.stream,
-                                      static_cast<uint32_t>(shape.slots * gemk::run_slot_bytes(variant)),
-                                      g->stream));
+        if (p.is_short) GEM_HIP(gemk::launch_short_run(a, variant, bf16, g->stream));
+        else GEM_HIP(gemk::launch_run(a, variant, bf16, stream_run(g, k, p.distinct),
+                                      static_cast<uint32_t>(p.slots * to.slot_bytes), g->stream));
         for (int j = 0; j < k; ++j) {
             g->pc[w[j]] = next_pull(g, g->t + j);
             if ((j0 + j) % K == 0) {

@@ -148,9 +148,11 @@ struct SegArgs {
 // first moments; General takes every mode as uniform runtime flags.
 enum class Variant { General = 0, Fast = 1, FastGlobal = 2 };
 
-// LDS of one slot of a run: a block's 1024 elements of a worker's snapshot and
-// moment (of its snapshot with the default rule's shared moment).
-constexpr int run_slot_bytes(Variant v) { return v == Variant::FastGlobal ? 4096 : 8192; }
+// LDS of one slot of a run.
+constexpr int run_slot_bytes(Variant v)
+{
+    return v == Variant::FastGlobal ? kRunSlotBytes / 2 : kRunSlotBytes;
+}
 
 // Launchers (defined in gem_kernels.hip).
 // depth: kPrefetchShallow, or kPrefetchDeep for (Generated, Fast, no

@@ -161,6 +161,9 @@ constexpr int kRunDstShift = 5;
 constexpr int kRunWorkerShift = 10;
 constexpr int32_t kRunMaxWorkers = 1 << (32 - kRunWorkerShift);
 constexpr int kRunMaxSlots = 31;
+// A slot: a block's 1024 elements of a worker's snapshot and moment (of its
+// snapshot, half of that, with the default rule's shared moment).
+constexpr int kRunSlotBytes = 8192;
 constexpr int32_t kRunMinLds = 64 << 10;   // LDS per compute unit the slots are sized for, at least
 constexpr int kRunWords = 996;
 constexpr int kRunCommits = kRunWords - kRunDepth;
@@ -256,6 +259,100 @@ inline int plan_short_run(const int32_t* worker, int k, uint32_t* words, int32_t
     for (int j = 0; j < k; ++j) slot_of[worker[j]] = -1;
     words[kRunWords - 1] = static_cast<uint32_t>(slots);
     return slots;
+}
+
+// ---- how a run is launched --------------------------------------------------------
+struct RunTarget {
+    int64_t Pp;       // padded elements of the vector
+    int cus;          // compute units (0 if unknown)
+    int lds_per_cu;   // LDS of a compute unit, bytes
+    int slot_bytes;   // of one of run_kernel's slots
+    bool adaptive;    // the launch carries staleness values
+};
+struct RunLaunch {
+    bool is_short;      // short_run_kernel, else run_kernel
+    int slots;          // LDS slots of a block
+    int64_t distinct;   // distinct workers
+    int moved;          // chunks read from memory plus chunks written to it, per block
+};
+
+// The most commits of one launch: as many as the argument block takes, and at
+// most 2^36 element-commits (a tenth of a second; 32 commits at least), so that a
+// launch over a very large vector does not keep the GPU from other streams for long.
+inline int run_commits(const RunTarget& to)
+{
+    const int64_t fit = to.adaptive ? kRunTauAt - kRunDepth : kRunCommits;
+    const int64_t cap = (int64_t{1} << 36) / to.Pp;
+    const int64_t most = cap > kPlanMaxK ? cap : kPlanMaxK;
+    return static_cast<int>(fit < most ? fit : most);
+}
+
+// Whether a launch of k commits by `distinct` workers goes to the short-vector
+// kernel, which holds all their rows in LDS.  It takes 0.12 us a commit for as
+// many blocks as are resident, up to 8 a compute unit with 20 workers and 2 with
+// 100; run_kernel takes 0.5 up to 262144 elements.  Past twice the resident blocks
+// or 8 a compute unit the latter's fewer instructions per element win.  Measured
+// (400 commits and the reads after them, short and run kernel, us): 20 workers,
+// 65536 elements 199 and 342, 131072: 257 and 345, 262144: 341 and 351, 524288:
+// 522 and 438; 100 workers, 32768: 192 and 343, 65536: 261 and 343, 131072: 386 and
+// 347; kappa = 2, 131072: 255 and 421.  With the compute units' number unknown
+// run_kernel takes every run.
+inline bool short_run(const RunTarget& to, int64_t distinct, int k)
+{
+    if (distinct > kShortSlots || to.cus < 1) return false;
+    const int64_t lds = short_run_lds(static_cast<int>(distinct), k, to.adaptive);
+    const int64_t per_cu = (to.Pp / kShortElems + to.cus - 1) / to.cus;
+    const int64_t most = 2 * (to.lds_per_cu / lds);
+    return per_cu <= (most < 8 ? most : 8);
+}
+
+// Plans a launch of k commits: the kernel, its slots, its schedule words.
+// run_kernel: 160 KiB of LDS per compute unit hold 20 slots (40 with the shared
+// moment's half slots), shared by the blocks resident there; measured at 12.5M
+// parameters, 988 commits, unless stated:
+//   - 4 blocks of 5 (10) slots when that holds every worker: nothing moves, and
+//     four waves per SIMD issue best (5 workers: 13.2 ms, 13.8 ms with 3 blocks,
+//     16.2 with 2);
+//   - 3 blocks of 6 slots while fewer than 0.68 of the commits move their rows (10
+//     workers: 15.6, 2 blocks 16.2; 11.7M, 50 workers, 400 commits, 0.61: 6.90, 7.21;
+//     25M, 64 workers, 160 commits, 0.67: 6.43, 6.60);
+//   - beyond, 2 blocks of 10 slots: fewer rows move, and the rows in flight have
+//     larger shares of the Infinity Cache (25M, 100 workers, 160 commits, 0.72:
+//     6.93, 3 blocks 7.39; 990 commits, 0.71: 40.3, 41.2; 124M, 64 workers, 160
+//     commits of a Pareto schedule, 0.86: 35.0, 38.1; 150 workers: 21.7, 25.2; 300:
+//     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
+//     (300 workers: 17.2, 2 blocks 18.1).
+// last: scratch of one int per worker (-1 on entry and on return).
+inline RunLaunch plan_launch(const RunTarget& to, const int32_t* worker, int k, uint32_t* words,
+                             int32_t* last)
+{
+    RunLaunch p{};
+    for (int j = 0; j < k; ++j) {
+        p.distinct += last[worker[j]] < 0;
+        last[worker[j]] = 0;
+    }
+    for (int j = 0; j < k; ++j) last[worker[j]] = -1;
+    p.is_short = short_run(to, p.distinct, k);
+    if (p.is_short) {
+        p.slots = plan_short_run(worker, k, words, last);
+        p.moved = 2 * p.slots;
+        return p;
+    }
+    constexpr int kLds = 160 << 10;
+    const bool shared = to.slot_bytes == kRunSlotBytes / 2;
+    const int all = (to.lds_per_cu < kLds ? to.lds_per_cu : kLds) / to.slot_bytes;
+    auto plan = [&](int blocks) {
+        p.slots = all / blocks;
+        if (p.slots < kRunDepth) p.slots = kRunDepth;
+        if (p.slots > kRunMaxSlots) p.slots = kRunMaxSlots;
+        p.moved = plan_run(worker, k, kRunDepth, p.slots, words, last);
+    };
+    if (p.distinct <= all / 4) plan(4);
+    else {
+        plan(3);
+        if (100 * p.moved >= 68 * 2 * k && !shared) plan(2);
+    }
+    return p;
 }
 
 }  // namespace gemk

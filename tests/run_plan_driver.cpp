@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <random>
+#include <set>
 #include <vector>
 
 #include "../paper_1805_08469_amd/csrc/gem_plan.hpp"
@@ -132,6 +133,45 @@ void check_short(const std::vector<int32_t>& w, int n)
         if (words[q] != 0xFFFFFFFFu) fail("short: word past the end", q, k, slots);
 }
 
+// The rules that pick a launch's kernel and slots, on devices with and without
+// known figures: the chosen kernel's LDS fits, an unknown number of compute
+// units leaves run_kernel, and the words are the plan's.
+void check_launch(const std::vector<int32_t>& w, int n)
+{
+    using namespace gemk;
+    const int k = static_cast<int>(w.size());
+    for (int cus : {0, 1, 256})
+        for (int lds : {kRunMinLds, 160 << 10})
+            for (int64_t Pp : {int64_t{64}, int64_t{64} * 8 * 256, int64_t{64} * 8 * 256 + 64, int64_t{1} << 31})
+                for (int slot_bytes : {kRunSlotBytes, kRunSlotBytes / 2})
+                    for (bool adaptive : {false, true}) {
+                        const RunTarget to{Pp, cus, lds, slot_bytes, adaptive};
+                        const int most = run_commits(to);
+                        if (most < kPlanMaxK || most > kRunCommits || (adaptive && most > kRunTauAt - kRunDepth))
+                            fail("commits of a launch", 0, most, lds);
+                        if (k > most) continue;
+                        std::vector<uint32_t> words(kRunWords, 0xFFFFFFFFu), again(words);
+                        std::vector<int32_t> last(n, -1);
+                        const RunLaunch p = plan_launch(to, w.data(), k, words.data(), last.data());
+                        for (int v : last)
+                            if (v != -1) fail("launch: scratch not restored", 0, k, p.slots);
+                        if (p.distinct != static_cast<int64_t>(std::set<int32_t>(w.begin(), w.end()).size()))
+                            fail("launch: distinct workers", 0, k, p.slots);
+                        if (p.is_short) {
+                            if (cus == 0 || Pp > int64_t{64} * 8 * cus) fail("launch: short kernel", 0, k, cus);
+                            if (static_cast<int64_t>(short_run_lds(p.slots, k, adaptive)) > lds ||
+                                p.slots != plan_short_run(w.data(), k, again.data(), last.data()) ||
+                                p.moved != 2 * p.slots)
+                                fail("launch: short plan", 0, k, p.slots);
+                        } else {
+                            if (p.slots < kRunDepth || p.slots > kRunMaxSlots || p.slots * slot_bytes > lds ||
+                                p.moved != plan_run(w.data(), k, kRunDepth, p.slots, again.data(), last.data()))
+                                fail("launch: run plan", 0, k, p.slots);
+                        }
+                        if (words != again) fail("launch: words", 0, k, p.slots);
+                    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -157,6 +197,7 @@ int main(int argc, char** argv)
         std::vector<int32_t> few(w);
         for (int32_t& x : few) x %= kShortSlots;
         check_short(few, std::min(n, kShortSlots));
+        if (rep % 10 == 0) check_launch(w, n);
         const int held = replay(w, n, depth, slots), most = most_waits(w, slots);
         // Waits shorter than depth are kept whatever they push out, so a plan may
         // hold fewer than the optimum only where such waits are.

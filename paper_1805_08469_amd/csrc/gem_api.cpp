@@ -59,9 +59,9 @@ struct gem_handle {
     gemk::SegUnit* units = nullptr;  // [nunits] what each block of the upper levels adds up
     int64_t nunits = 0;
     int32_t seg_teams = 1;           // teams of 256 threads in such a block
-    double* sup = nullptr;           // [3][nsup] index-block sums
+    double* sup = nullptr;           // [3][nsup] index-block sums of segments of several blocks
     float* pi_seg = nullptr;         // [nseg]
-    uint32_t* seg_done = nullptr;    // [nseg] pair blocks finished in the running launch
+    uint32_t* seg_done = nullptr;    // [nseg] blocks of a segment finished in the running launch
     int32_t lds_per_cu = 0;          // LDS of a compute unit, bytes (0 if unknown)
     uint32_t deep_lds = 0;           // LDS reserved per block of the deep-ring pass
     int32_t cus = 0;                 // compute units of the device (0 if unknown)
@@ -424,27 +424,20 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
     auto index_blocks = [&](int32_t k) {
         return (off[k + 1] - 1) / gemk::kSegBlock - off[k] / gemk::kSegBlock + 1;
     };
-    int64_t nsup = 0, most = 0;
+    int64_t most = 0;
     for (int32_t k = 0; k < nseg; ++k) most = std::max(most, index_blocks(k));
     const int teams = most > 1 && nseg <= gemk::kSegUnitMost ? gemk::kSegTeams : 1;
-    std::vector<gemk::SegUnit> units;
+    int64_t nunits = 0, nsup = 0;   // (a segment of one unit needs no room for its sums, so nsup may be 0)
+    for (int32_t k = 0; k < nseg; ++k) nunits += (index_blocks(k) + teams - 1) / teams;
+    std::vector<gemk::SegUnit> units(static_cast<size_t>(nunits));
+    gemk::SegUnit* next = units.data();
     for (int32_t k = 0; k < nseg; ++k) {
-        gemk::SegUnit u{};
-        u.part_first = part_off[k];
-        u.g_lo = off[k] / gemk::kSegGroup;
-        u.g_hi = (off[k + 1] - 1) / gemk::kSegGroup;
-        u.size = off[k + 1] - off[k];
-        u.sup_first = nsup;
-        u.sup_count = index_blocks(k);
-        u.units = static_cast<int32_t>((u.sup_count + teams - 1) / teams);
-        u.seg = k;
-        for (int64_t b = 0; b < u.sup_count; b += teams) {
-            u.sup_at = nsup + b;
-            u.blk0 = off[k] / gemk::kSegBlock + b;
-            u.nblk = static_cast<int32_t>(std::min<int64_t>(teams, u.sup_count - b));
-            units.push_back(u);
-        }
-        nsup += u.sup_count;
+        const int64_t blocks = index_blocks(k);
+        for (int64_t b = 0; b < blocks; b += teams)
+            *next++ = {static_cast<uint32_t>(off[k]), static_cast<uint32_t>(off[k + 1] - off[k]),
+                       static_cast<uint32_t>(part_off[k]), static_cast<uint32_t>(nsup), k,
+                       static_cast<int32_t>(b)};
+        if (blocks > teams) nsup += blocks;
     }
     std::vector<int32_t> gseg(static_cast<size_t>(groups));
     int32_t k = 0;
@@ -461,7 +454,7 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
               hipMalloc(&g->part, static_cast<size_t>(3 * npart * gemk::kWavesPerGroup) *
                                       sizeof(double)) == hipSuccess &&
               hipMalloc(&g->units, units.size() * sizeof(gemk::SegUnit)) == hipSuccess &&
-              hipMalloc(&g->sup, static_cast<size_t>(3 * nsup) * sizeof(double)) == hipSuccess &&
+              hipMalloc(&g->sup, static_cast<size_t>(3 * nsup + 1) * sizeof(double)) == hipSuccess &&
               hipMalloc(&g->pi_seg, static_cast<size_t>(nseg) * sizeof(float)) == hipSuccess &&
               hipMalloc(&g->seg_done, static_cast<size_t>(nseg) * sizeof(uint32_t)) == hipSuccess;
     if (!ok) {
@@ -471,7 +464,7 @@ int build_segments(gem_handle* g, const std::vector<int64_t>& off)
     }
     g->npart = npart;
     g->nsup = nsup;
-    g->nunits = static_cast<int64_t>(units.size());
+    g->nunits = nunits;
     g->seg_teams = teams;
     const int rc = [&]() -> int {
         GEM_HIP(hipMemcpyAsync(g->seg_off, off.data(), off.size() * sizeof(int64_t),

@@ -190,19 +190,17 @@ struct SegFactors {
 };
 // The part of a segment that one block of seg_blocks_kernel adds up: up to
 // `teams` consecutive index blocks (kSegBlock indices each) of it.
+// (24 bytes: a partition may have as many segments as parameters, and the block
+// works the rest out in a few scalar instructions.)
 struct SegUnit {
-    int64_t part_first;   // the segment's first slot of group sums
-    int64_t g_lo, g_hi;   // the segment's first and last group
-    int64_t size;         // the segment's elements
-    int64_t sup_at;       // where this unit's index-block sums go
-    int64_t sup_first;    // the segment's first index-block sum,
-    int64_t sup_count;    // and how many it has
-    int64_t blk0;         // the unit's first index block
-    int32_t nblk;         // and how many it has
-    int32_t units;        // units of the segment
+    uint32_t lo;          // the segment's first element
+    uint32_t size;        // and how many it has
+    uint32_t part_first;  // the segment's first slot of group sums
+    uint32_t sup_first;   // its first index-block sum (a segment of several units)
     int32_t seg;
-    int32_t pad_;
+    int32_t blk;          // the unit's first index block, counted from the segment's
 };
+static_assert(GEM_P_MAX <= (INT64_C(1) << 31), "elements and slots of sums fit 32 bits");
 // Teams of 256 threads in a block, unless no segment has more than one index block
 // or there are too many segments (kSegUnitMost) for blocks of 1024 threads: then 1.
 constexpr int kSegTeams = 4;

@@ -1414,12 +1414,18 @@ __global__ __launch_bounds__(TEAMS* kBlock) void seg_blocks_kernel(const double*
     __shared__ double tail[3][64];
     __shared__ int last;
     const SegUnit u = units[blockIdx.x];
-    if (static_cast<int>(threadIdx.x >> 8) < u.nblk) {
-        const int64_t grp = (u.blk0 + (threadIdx.x >> 8)) * int64_t{kBlock} + (threadIdx.x & 255);
+    const uint32_t hi = u.lo + (u.size - 1u);                       // the segment's last element
+    const uint32_t seg_blk = u.lo / static_cast<uint32_t>(kSegBlock);
+    const int sup_count = static_cast<int>(hi / static_cast<uint32_t>(kSegBlock) - seg_blk) + 1;
+    const int nblk = sup_count - u.blk < TEAMS ? sup_count - u.blk : TEAMS;
+    if (static_cast<int>(threadIdx.x >> 8) < nblk) {
+        const uint32_t grp = (seg_blk + u.blk + (threadIdx.x >> 8)) * kBlock + (threadIdx.x & 255);
+        const uint32_t g_lo = u.lo / static_cast<uint32_t>(kSegGroup);
+        const uint32_t g_hi = hi / static_cast<uint32_t>(kSegGroup);
         double va = 0.0, vm = 0.0, vd = 0.0;
-        if (grp >= u.g_lo && grp <= u.g_hi) {
+        if (grp >= g_lo && grp <= g_hi) {
             // the group's four wave sums, (w0 + w1) + (w2 + w3)
-            const int64_t q = (u.part_first + (grp - u.g_lo)) * kWavesPerGroup;
+            const int64_t q = (int64_t{u.part_first} + (grp - g_lo)) * kWavesPerGroup;
             const int64_t stride = npart * kWavesPerGroup;
             const double* pa = part + q;
             const double* pm = part + stride + q;
@@ -1448,22 +1454,23 @@ __global__ __launch_bounds__(TEAMS* kBlock) void seg_blocks_kernel(const double*
         const double* l = &lds[kind][4 * p];
         return (l[0] + l[1]) + (l[2] + l[3]);
     };
-    if (u.units == 1) {
+    if (sup_count <= TEAMS) {
         if (threadIdx.x >= 64) return;
         double sum = 0.0;
-        for (int p = 0; p < u.nblk; ++p) sum = sum + pair_sum(p);
+        for (int p = 0; p < nblk; ++p) sum = sum + pair_sum(p);
         segment_factor(u.seg, u.size, sum, f);
         return;
     }
     if (threadIdx.x < 64) {
         if (threadIdx.x < 3)
-            for (int p = 0; p < u.nblk; ++p) sup[kind * nsup + u.sup_at + p] = pair_sum(p);
+            for (int p = 0; p < nblk; ++p)
+                sup[kind * nsup + u.sup_first + u.blk + p] = pair_sum(p);
         if (threadIdx.x == 0) last = 0;
         __threadfence();   // release this block's sums to every XCD
         wave_sync();
         if (threadIdx.x == 0) {
             const uint32_t done = atomicAdd(&seg_done[u.seg], 1u) + 1u;
-            last = done == static_cast<uint32_t>(u.units);
+            last = done == static_cast<uint32_t>((sup_count + TEAMS - 1) / TEAMS);
             if (last) atomicExch(&seg_done[u.seg], 0u);
         }
     }
@@ -1471,17 +1478,17 @@ __global__ __launch_bounds__(TEAMS* kBlock) void seg_blocks_kernel(const double*
     if (!last || threadIdx.x >= 64) return;
     __threadfence();       // acquire the other blocks' sums
     double sum = 0.0;
-    for (int64_t base = 0; base < u.sup_count; base += 64) {
+    for (int base = 0; base < sup_count; base += 64) {
         // the lanes load 64 index blocks' sums of each kind at once; lanes 0 to
         // 2 then add a kind each, in order (one wave: its LDS accesses stay in order)
-        const int64_t q = base + threadIdx.x;
-        if (q < u.sup_count) {
+        const int q = base + static_cast<int>(threadIdx.x);
+        if (q < sup_count) {
             tail[0][threadIdx.x] = sup[u.sup_first + q];
             tail[1][threadIdx.x] = sup[nsup + u.sup_first + q];
             tail[2][threadIdx.x] = sup[2 * nsup + u.sup_first + q];
         }
         wave_sync();
-        const int cnt = (u.sup_count - base < 64) ? static_cast<int>(u.sup_count - base) : 64;
+        const int cnt = sup_count - base < 64 ? sup_count - base : 64;
         for (int k = 0; k < cnt; ++k) sum = sum + tail[kind][k];
         wave_sync();
     }

@@ -196,6 +196,32 @@ def _device_rows(torch, arr):
     return buf, [buf[j].data_ptr() for j in range(K)]
 
 
+def test_device_memory_of_a_fine_partition(G):
+    """Two million segments of one element: the partition's device tables take at
+    most 160 bytes a segment (96 of them the wave sums of each segment's one
+    group), and the commits equal element-wise ones, which read the same factors."""
+    import torch
+    from paper_1805_08469_amd.workloads import make_problem
+    P, n = 2_000_003, 2
+    h, ts = make_problem(P, 1e-3, 1.0, 5)
+    states = {}
+    for scope in (G.GEM_PI_SEGMENT, G.GEM_PI_ELEMENT):
+        with G.Gem(P, n, _hp(G, pi_scope=scope)) as g:
+            g.set_quadratic(h, ts, 0.01, 0.1, 3)
+            if scope == G.GEM_PI_SEGMENT:
+                torch.cuda.synchronize()
+                before = torch.cuda.mem_get_info()[0]
+                g.set_segments(np.arange(P + 1, dtype=np.int64))
+                torch.cuda.synchronize()
+                used = before - torch.cuda.mem_get_info()[0]
+                print(f"[segments] {used / P:.1f} bytes a segment", flush=True)
+                assert used <= 160 * P + (16 << 20)      # (each allocation rounds up)
+            g.sim_run(np.array([0, 1, 0], np.int32), None, 1)
+            states[scope] = (g.theta(), g.S(), g.M())
+    for a, b in zip(states[G.GEM_PI_SEGMENT], states[G.GEM_PI_ELEMENT]):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_given_updates(G, dtype):
     import torch

@@ -26,6 +26,14 @@ def parity(gpu, ref):
     return float(rel.max()) if rel.size else 0.0, int((~same_bits).sum())
 
 
+def sim_passes(g, worker, tau, K):
+    """The run as successive calls of at most K commits.  Each is one pass and
+    goes to the pass kernels, where one call of them all would go to the run
+    kernels."""
+    for j in range(0, len(worker), K):
+        g.sim_run(worker[j:j + K], tau[j:j + K], K)
+
+
 def assert_parity(name, gpu, ref, tol=1e-5):
     """The parity bar: max relative error <= 1e-5; the design makes every
     entry bit-identical, which is checked too."""

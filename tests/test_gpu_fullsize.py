@@ -1,9 +1,10 @@
 """Parity at the workloads' full sizes, in the launch configuration the
-benchmark times (gem_sim_run over the whole schedule with the workload's K).
+benchmark times (gem_sim_run over the whole schedule with the workload's K: the
+run kernels), and in calls of one pass (the pass kernels).
 
 The GPU runs every element; the oracle runs a sample of element indices: one
 index in every block of 1024 elements (the elements one 256-thread block of
-the pass owns, whose tile base and row offsets are block-uniform), at a lane
+the pass or run kernel owns, whose tile base and row offsets are block-uniform), at a lane
 position that rotates through all 1024 positions, both sides of every
 8192-element table-tile edge, the first and last chunks, the ragged tail and
 random indices.  Each element's trajectory depends only on its own inputs,
@@ -13,7 +14,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_util import assert_parity
+from gpu_util import assert_parity, sim_passes
 
 pytestmark = pytest.mark.gpu
 
@@ -74,7 +75,7 @@ def test_recording_past_16_bit_counts(G):
     assert np.array_equal(hist.astype(np.int64), want)
 
 
-def _workload_parity(G, name, T=None, proxy=0):
+def _workload_parity(G, name, T=None, proxy=0, passes=False):
     from paper_1805_08469_amd.workloads import WORKLOADS, problem
     wl = WORKLOADS[name]
     if T is not None:
@@ -91,7 +92,10 @@ def _workload_parity(G, name, T=None, proxy=0):
     ghp.proxy_mode = proxy
     with G.Gem(wl.P, wl.n, ghp) as g:
         g.set_quadratic(h, ts, wl.lr, wl.sigma, wl.seed, bf16=wl.bf16)
-        g.sim_run(worker, tau, wl.K)
+        if passes:
+            sim_passes(g, worker, tau, wl.K)
+        else:
+            g.sim_run(worker, tau, wl.K)
         theta, S, M = g.gather(idx)
         pc = g.pull_clocks()
         stats = g.stats()
@@ -104,6 +108,16 @@ def _workload_parity(G, name, T=None, proxy=0):
     assert_parity(f"{name} S", S, st.S)
     assert_parity(f"{name} M", M, st.M)
     return stats
+
+
+@pytest.mark.parametrize("name,T,proxy", [("small", 500, 0), ("resnet18", 203, 0),
+                                          ("headline", 321, 0), ("headline", 321, 1),
+                                          ("large", 33, 0)])
+def test_passes(G, name, T, proxy):
+    """The pass kernels at full size: the single-commit kernel, the shallow and the
+    deep ring, streaming and cached, with a shorter last pass."""
+    s = _workload_parity(G, name, T, proxy, passes=True)
+    assert s.commits == T
 
 
 def test_small(G):
@@ -133,7 +147,8 @@ def test_large(G):
 def test_largest_vector(G):
     """The largest P the library takes, less 3 (ragged: not a multiple of the
     16-byte chunk, the 1024-element block or the 8192-element tile), two
-    workers, 33 commits in passes of 32 and 1.  Element indices near 2^31 and
+    workers, 33 commits as a pass of 16, a run of 16 (two passes of 8) and a
+    single commit.  Element indices near 2^31 and
     table offsets past 2^33 bytes must reach the right elements.  The oracle
     runs one index per block of the top 2^24 elements, both sides of every
     tile edge there, the last 16 elements, indices around 2^29 and 2^30 and
@@ -141,7 +156,7 @@ def test_largest_vector(G):
     pattern every 2^20 elements, scaled and shifted per 2^20-element span, so
     no two spans hold the same values."""
     P = G.GEM_P_MAX - 3
-    n, T, K = 2, 33, 32
+    n, T = 2, 33
     need = 4 * P * (2 * n + 3) * 1.05
     if _free_bytes() < need:
         pytest.skip(f"needs {need / 2**30:.1f} GiB of device memory")
@@ -165,13 +180,14 @@ def test_largest_vector(G):
     idx = np.concatenate([fixed, per_block, edges - 1, edges, np.arange(P - 16, P),
                           rng.integers(0, P, size=20_000)])
     idx = np.unique(idx[(idx >= 0) & (idx < P)]).astype(np.int64)
-    print(f"[largest] P={P} n={n} T={T} K={K} sample={idx.size}", flush=True)
+    print(f"[largest] P={P} n={n} T={T} sample={idx.size}", flush=True)
     with G.Gem(P, n) as g:
         g.set_quadratic(h, ts, 0.01, 0.02, 5)
-        g.sim_run(worker, tau, K)
+        for a, b, K in ((0, 16, 16), (16, 32, 8), (32, 33, 1)):
+            g.sim_run(worker[a:b], tau[a:b], K)
         theta, S, M = g.gather(idx)
         stats = g.stats()
-    assert stats.passes == 2 and stats.commits == T
+    assert stats.passes == 4 and stats.commits == T
     hp = O.Hyper(lr=0.01, sigma=0.02, momentum=0.9, seed=5)
     st = O.State.initial(n, idx.size)
     O.run(hp, P, st, idx, h[idx], ts[idx], worker, tau)

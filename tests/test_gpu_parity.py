@@ -1,5 +1,5 @@
-"""GPU parity of whole simulated runs (gem_sim_run) against the oracle:
-theta, every worker's snapshot S[w] and moment M[w], element by element, on
+"""GPU parity of whole simulated runs (gem_sim_run) against the oracle, as one
+call (the run kernels) and as calls of one pass (the pass kernels): theta, every worker's snapshot S[w] and moment M[w], element by element, on
 the same seeded schedules and noise.  Covers the tiny workload end to end,
 fusion of K commits per pass (with workers repeating inside a pass at every
 distance), ragged parameter counts, every commit-rule mode,
@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_util import assert_parity, parity
+from gpu_util import assert_parity, parity, sim_passes
 
 pytestmark = pytest.mark.gpu
 
@@ -43,10 +43,19 @@ def _run_both(G, P, n, worker, tau, K, hp, lr=0.01, sigma=0.1, seed=7, bf16=Fals
               h_lo=1e-3, pseed=1):
     from paper_1805_08469_amd.workloads import make_problem
     h, ts = make_problem(P, h_lo, 1.0, pseed)
-    with G.Gem(P, n, hp) as g:
-        g.set_quadratic(h, ts, lr, sigma, seed, bf16=bf16)
-        g.sim_run(worker, tau, K)
-        out = (g.theta(), g.S(), g.M(), g.pull_clocks(), g.clock, g.stats())
+    # one call, then the same as one call a pass (whose result is returned)
+    for one_call in (True, False):
+        with G.Gem(P, n, hp) as g:
+            g.set_quadratic(h, ts, lr, sigma, seed, bf16=bf16)
+            if one_call:
+                g.sim_run(worker, tau, K)
+            else:
+                run = out
+                sim_passes(g, worker, tau, K)
+            out = (g.theta(), g.S(), g.M(), g.pull_clocks(), g.clock, g.stats())
+    for name, a, b in zip(("theta", "S", "M", "pull clocks"), run, out):
+        assert_parity(f"one call, {name}", a, b)
+    assert run[4] == out[4] and run[5].passes == -(-len(worker) // K)
     st = O.State.initial(n, P)
     O.run(_ohp(hp, lr, sigma, seed, bf16), P, st, np.arange(P), h, ts, worker, tau)
     return out, st
@@ -202,7 +211,8 @@ def test_cache_policies_give_the_same_bits(G, case, mode, K, bf16):
     """Streaming (non-temporal) and default-policy passes give the same state,
     bit for bit, equal to the oracle -- every pass variant and ring depth, with
     repeats and evictions inside passes (a small state, where AUTO keeps the
-    default policy and STREAM is forced)."""
+    default policy and STREAM is forced).  (The run kernel's policies are
+    compared in test_gpu_runs.py.)"""
     P, n, T = 8192 * 2 + 77, 5, 160
     hp = _hp(G, **mode)
     worker, tau = G.gem_schedule_make(n, T, G.GEM_LAW_EXP, seed=31, pull_mode=hp.pull_mode)
@@ -213,7 +223,7 @@ def test_cache_policies_give_the_same_bits(G, case, mode, K, bf16):
         with G.Gem(P, n, hp) as g:
             g.set_cache_policy(policy)
             g.set_quadratic(h, ts, 0.01, 0.1, 9, bf16=bf16)
-            g.sim_run(worker, tau, K)
+            sim_passes(g, worker, tau, K)
             states[policy] = (g.theta(), g.S(), g.M())
     for policy in (G.GEM_CACHE_STREAM, G.GEM_CACHE_AUTO):
         for a, b in zip(states[G.GEM_CACHE_KEEP], states[policy]):
@@ -227,8 +237,9 @@ def test_cache_policies_give_the_same_bits(G, case, mode, K, bf16):
 
 @pytest.mark.parametrize("mode", [{}, dict(proxy=1)], ids=["default", "global_proxy"])
 def test_single_commit_tail_pass(G, mode):
-    """A run whose last pass holds one commit (T = 2K + 1) switches to the
-    single-commit kernel for it; the state still equals the oracle's."""
+    """A run in calls of one pass whose last pass holds one commit (T = 2K + 1)
+    switches to the single-commit kernel for it; the state still equals the
+    oracle's."""
     P, n, K = 8192 + 129, 6, 32
     T = 2 * K + 1
     hp = _hp(G, **mode)
@@ -237,7 +248,7 @@ def test_single_commit_tail_pass(G, mode):
     h, ts = make_problem(P, 1e-3, 1.0, 5)
     with G.Gem(P, n, hp) as g:
         g.set_quadratic(h, ts, 0.01, 0.1, 4)
-        g.sim_run(worker, tau, K)
+        sim_passes(g, worker, tau, K)
         out = (g.theta(), g.S(), g.M(), g.clock)
     assert out[3] == T
     st = O.State.initial(n, P)

@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from gpu_util import assert_parity
+from gpu_util import assert_parity, sim_passes
 
 pytestmark = pytest.mark.gpu
 
@@ -42,10 +42,22 @@ def _check(g, st, tag):
     assert_parity(f"{tag} M", g.M(), st.M)
 
 
+def _run(g, worker, tau, K, calls):
+    """The schedule in one call, or in one call a pass (see sim_passes)."""
+    if calls == "one":
+        g.sim_run(worker, tau, K)
+    else:
+        sim_passes(g, worker, tau, K)
+
+
+CALLS = pytest.mark.parametrize("calls", ["one", "passes"])
+
+
+@CALLS
 @pytest.mark.parametrize("K", [2, 32])
-def test_single_worker(env, K):
+def test_single_worker(env, K, calls):
     """n = 1: zero staleness, and every commit after the first in a pass takes
-    the worker's rows from registers."""
+    the worker's rows from registers (in a run, from LDS)."""
     _, G = env
     from paper_1805_08469_amd.workloads import make_problem
     P, T = 5000, 200
@@ -55,18 +67,20 @@ def test_single_worker(env, K):
     st = O.State.initial(1, P)
     with G.Gem(P, 1) as g:
         g.set_quadratic(h, ts, 0.02, 0.1, 4)
-        g.sim_run(worker, tau, K)
+        _run(g, worker, tau, K, calls)
         O.run(O.Hyper(lr=0.02, sigma=0.1, seed=4), P, st, np.arange(P), h, ts, worker, tau)
         _check(g, st, f"n=1 K={K}")
         assert g.stats().passes == -(-T // K)
 
 
+@CALLS
 @pytest.mark.parametrize("proxy", ["local", "global"])
-def test_near_repeats_evict_far_held_rows(env, proxy):
+def test_near_repeats_evict_far_held_rows(env, proxy, calls):
     """Four workers held in the register slots for a far repeat, then workers
     that commit twice in a row: each near repeat takes the slot of the held
     chunk used furthest ahead, which goes back to memory and is read again
-    through the ring.  No pass is cut, and the state equals the oracle."""
+    through the ring.  No pass is cut, and the state equals the oracle.  (That
+    is the pass kernels; one call of them all is a run.)"""
     _, G = env
     from paper_1805_08469_amd.workloads import make_problem
     P, n = 4133, 8
@@ -79,14 +93,15 @@ def test_near_repeats_evict_far_held_rows(env, proxy):
     st = O.State.initial(n, P)
     with G.Gem(P, n, hp) as g:
         g.set_quadratic(h, ts, 0.01, 0.1, 6)
-        g.sim_run(worker, tau, 32)
+        _run(g, worker, tau, 32, calls)
         O.run(O.Hyper(lr=0.01, sigma=0.1, seed=6, proxy=int(hp.proxy_mode)), P, st,
               np.arange(P), h, ts, worker, tau)
         _check(g, st, f"evictions ({proxy} proxy)")
         assert g.stats().passes == worker.size // 32
 
 
-def test_no_repeats_in_a_pass(env):
+@CALLS
+def test_no_repeats_in_a_pass(env, calls):
     """n = 320 workers in a permuted round robin: every pass of 32 commits moves
     32 distinct workers' rows (no register slot is ever used)."""
     _, G = env
@@ -99,7 +114,7 @@ def test_no_repeats_in_a_pass(env):
     st = O.State.initial(n, P)
     with G.Gem(P, n) as g:
         g.set_quadratic(h, ts, 0.01, 0.1, 5)
-        g.sim_run(worker, tau, 32)
+        _run(g, worker, tau, 32, calls)
         O.run(O.Hyper(lr=0.01, sigma=0.1, seed=5), P, st, np.arange(P), h, ts, worker, tau)
         _check(g, st, "no repeats")
         assert g.stats().passes == worker.size // 32

@@ -1,22 +1,22 @@
 #!/usr/bin/env python3
 """Benchmark of the GEM commit pipeline on one MI355X.
 
-One step is one simulated run of the workload's T commits: gem_sim_run plans
-the passes (validation, snapshot routing) and launches the fused
-stale-gradient + GEM-commit pass kernel once per K commits.  The schedule of
-the asynchronous system (which worker commits when, with what staleness) is
-the synthetic input: it is drawn by the library's host schedule generator
-before timing, for warmup + steps consecutive runs, so the system keeps
-running across steps.  The problem (h, theta*) is resident in HBM before the
-timed region.
+One step is one simulated run of the workload's T commits: one gem_sim_run,
+which takes up to 993 of them in a launch of its run kernels (--calls pass: one
+call, and launch, per pass of K commits).  The schedule of the asynchronous
+system (which worker commits when, with what staleness) is the synthetic input:
+it is drawn by the library's host schedule generator before timing, for warmup
++ steps consecutive runs, so the system keeps running across steps.  The
+problem (h, theta*) is resident in HBM before the timed region.
 
-Prints one JSON line: parameter-commits/s (P x commits/s) and the fused
-pass's algorithmic HBM bandwidth against the 8 TB/s peak, with the CPU oracle
-timed on a bounded sample as a reported baseline.
+Prints one JSON line: parameter-commits/s (P x commits/s), what its launches
+read and write against the 8 TB/s peak, and their compute floor, with the CPU
+oracle timed on a bounded sample as a reported baseline.
 """
 from __future__ import annotations
 
 import argparse
+import ctypes
 import hashlib
 import json
 import os
@@ -31,28 +31,30 @@ HBM_PEAK_GBS = 8000.0
 # VALU issue ceiling of one MI355X: the fp32 vector peak, 157.3 TFLOP/s =
 # 256 CUs x 2.4 GHz x 256 flop per CU and cycle, is two wave64 FMA
 # instructions (128 flop each) per CU and cycle: 1228.8 G wave64 VALU
-# instructions per second.  Instructions slower than a full-rate FMA (64-bit
-# integer multiplies, transcendental approximations) only lower what a real
-# instruction mix can reach.
+# instructions per second.  One wave issues an instruction every four cycles; a
+# SIMD with several waves reaches 970 G/s (at the clock it then runs at) with
+# additions, multiplications, FMAs of vector registers and logic, 520-550 with
+# 64-bit multiply-adds, conversions, comparisons, shifts, three-operand minima
+# and maxima and FMAs with a scalar operand, and 290 with reciprocals and roots
+# (measured, 8 waves per SIMD): a real instruction mix reaches less than the peak.
 VALU_PEAK_GINST = 256 * 2.4 * 2
-# The same figure counts two lanes' FMAs per packed-FP32 instruction slot; the
-# library builds without packed FP32, and its integer and unpacked instructions
-# issue at one wave64 instruction per SIMD every four cycles: 4 SIMDs x 256 CUs
-# x 2.4 GHz / 4 = 614.4 G/s (the fp64 vector rate, 78.6 TFLOP/s, in the same
-# units).
-VALU_ISSUE_GINST = 256 * 2.4
 METRIC = "parameter-commits/s (P×commits/s) + achieved HBM GB/s vs peak, P=25M n=100"
 KERNEL_SOURCES = ("gem_kernels.hip", "gem_device.hpp", "gem_internal.hpp", "gem_plan.hpp",
                   "gem_layout.hpp")
-# Committed rocprofv3 counter summaries of the dominant kernel, per (workload,
-# proxy, pi scope), each taken with the library's own cache rule.
+# Committed rocprofv3 counter summaries of the dominant kernel, per (kernel,
+# workload, proxy), each taken with the library's own cache rule.
 COUNTERS_FILES = {
-    ("headline", "local", "element"): "pass_kernel_headline_counters.md",
-    ("headline", "global", "element"): "pass_kernel_headline_global_proxy_counters.md",
-    ("small", "local", "element"): "pass_kernel_small_counters.md",
-    ("resnet18", "local", "element"): "pass_kernel_resnet18_counters.md",
-    ("large", "local", "element"): "pass_kernel_large_counters.md",
-    ("headline", "local", "segment"): "seg_step_kernel_headline_counters.md",
+    ("run_kernel", "headline", "local"): "run_kernel_headline_counters.md",
+    ("run_kernel", "headline", "global"): "run_kernel_headline_global_proxy_counters.md",
+    ("run_kernel", "small", "local"): "run_kernel_small_counters.md",
+    ("run_kernel", "resnet18", "local"): "run_kernel_resnet18_counters.md",
+    ("run_kernel", "large", "local"): "run_kernel_large_counters.md",
+    ("pass_kernel", "headline", "local"): "pass_kernel_headline_counters.md",
+    ("pass_kernel", "headline", "global"): "pass_kernel_headline_global_proxy_counters.md",
+    ("pass_kernel", "small", "local"): "pass_kernel_small_counters.md",
+    ("pass_kernel", "resnet18", "local"): "pass_kernel_resnet18_counters.md",
+    ("pass_kernel", "large", "local"): "pass_kernel_large_counters.md",
+    ("seg_step_kernel", "headline", "local"): "seg_step_kernel_headline_counters.md",
 }
 
 
@@ -70,11 +72,11 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_counters(workload: str, proxy: str, scope: str):
+def measured_counters(kernel: str, workload: str, proxy: str):
     """The machine-readable block of the committed rocprofv3 counter summary
-    for this configuration (HBM bytes and VALU instructions per launch of the
+    for this configuration (memory bytes and VALU instructions per launch of the
     dominant kernel), if it was taken on the current kernel source; else None."""
-    name = COUNTERS_FILES.get((workload, proxy, scope))
+    name = COUNTERS_FILES.get((kernel, workload, proxy))
     path = os.path.join(ROOT, "profiles", name) if name else None
     if path is None or not os.path.exists(path):
         return None
@@ -83,10 +85,32 @@ def measured_counters(workload: str, proxy: str, scope: str):
     if not m:
         return None
     d = json.loads(m.group(1))
-    if (d.get("kernel_hash") != kernel_hash() or d.get("workload") != workload
-            or d.get("proxy", "local") != proxy or d.get("pi_scope", "element") != scope):
+    if (d.get("kernel_hash") != kernel_hash() or d.get("kernel") != kernel
+            or d.get("workload") != workload or d.get("proxy") != proxy):
         return None
     return d
+
+
+SELFTEST_LIB = os.path.join(ROOT, "paper_1805_08469_amd", "libgem_selftest.so")
+
+
+def run_plan(wl, worker, shared: bool, adaptive: bool, cus: int = 0, lds: int = 0) -> dict:
+    """The launches of one gem_sim_run of these commits, and the bytes their
+    plans move between memory and the chip: theta, h and theta* once a launch,
+    and each row that is not kept in LDS between two commits of its worker."""
+    import numpy as np
+    L = ctypes.CDLL(SELFTEST_LIB)
+    w = np.ascontiguousarray(worker, dtype=np.int32)
+    out = (ctypes.c_int64 * 4)()
+    rc = L.gem_selftest_run_plan(ctypes.c_int64(wl.P), wl.n, int(shared), int(adaptive),
+                                 w.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(w.size), cus,
+                                 lds, out)
+    if rc != 0:
+        raise RuntimeError(f"gem_selftest_run_plan: {rc}")
+    launches, short, streaming, rows = out
+    Pp = -(-wl.P // 64) * 64
+    return {"launches": launches, "short": short, "streaming": streaming,
+            "bytes": Pp * (launches * (24 if shared else 16) + rows * (4 if shared else 8))}
 
 
 def host_description() -> dict:
@@ -151,19 +175,21 @@ def copy_ceiling(G, torch, nbytes: int, reps: int = 10) -> float:
     return 2 * nbytes / (ms * 1e-3) / 1e9
 
 
-def compute_floor(G, torch, wl, hp, cache: int, pi_hist: bool) -> float:
+def compute_floor(G, torch, wl, hp, cache: int, pi_hist: bool, calls: str) -> float:
     """Milliseconds of compute per commit of the workload's kernel: the same
-    kernel over the same P with two workers in turn (when recording, with one).
+    kernel over the same P with two workers in turn (in passes, with one).
     Their snapshots and moments stay on the chip for the whole launch, so its
-    time is the noise generator's and the commit arithmetic's.  (One worker
-    alone waits on its own rows: each of its commits starts from the last one's
-    result.)  A real configuration of the method, run through gem_sim_run; over
-    a short vector with as many commits as keep a launch's start a small part."""
+    time is the noise generator's and the commit arithmetic's.  (In a run, one
+    worker alone waits on its own rows: each of its commits starts from the last
+    one's result.)  A real configuration of the method, run through gem_sim_run;
+    over a short vector with as many commits as keep a launch's start a small
+    part."""
     import numpy as np
     stream = torch.cuda.current_stream()
     K = G.GEM_K_MAX
     T = (62 if wl.P < 1 << 20 else 12) * K
-    workers = 1 if pi_hist else 2
+    passes = pi_hist or calls == "pass"
+    workers = 1 if passes else 2
     worker = np.arange(T, dtype=np.int32) % workers
     with G.Gem(wl.P, workers, hp, stream=stream.cuda_stream) as g:
         g.set_cache_policy(cache)
@@ -171,10 +197,12 @@ def compute_floor(G, torch, wl, hp, cache: int, pi_hist: bool) -> float:
         g.sim_run(worker if wl.P < 1 << 20 else worker[:2 * K], None, K)    # warm-up
         if pi_hist:
             G.gem_pi_hist_start(g.h, T)
+        each = K if passes else T
         torch.cuda.synchronize()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record(stream)
-        g.sim_run(worker, None, K)
+        for j in range(0, T, each):
+            g.sim_run(worker[j:j + each], None, K)
         e1.record(stream)
         torch.cuda.synchronize()
     return e0.elapsed_time(e1) / T
@@ -253,6 +281,9 @@ def main() -> int:
     ap.add_argument("--pi-hist", action="store_true",
                     help="record the per-commit histograms of the scale factor during the timed "
                          "steps (the diagnostic kernel variant)")
+    ap.add_argument("--calls", default="run", choices=["run", "pass"],
+                    help="run: a step is one gem_sim_run; pass: one for each pass of K commits, "
+                         "which runs the pass kernels")
     ap.add_argument("--cache", default="auto", choices=["auto", "keep", "stream"],
                     help="cache policy of the passes: the library's rule (stream when the state "
                          "outgrows the Infinity Cache), the default policy, or streaming")
@@ -310,9 +341,11 @@ def main() -> int:
     hp.pi_scope = G.GEM_PI_SEGMENT if args.pi_scope == "segment" else G.GEM_PI_ELEMENT
     fast = (args.rule, args.pi, args.kappa, args.pi_scope) == ("gem", "clamp0", 1.0, "element")
     variant = "General" if not fast else "FastGlobal" if args.proxy == "global" else "Fast"
-    # The library's ring depth for these passes (deep: the default rule with
+    # The library's ring depth for its passes (deep: the default rule with
     # per-worker moments in passes of at least 16 commits).
     depth = 4 if variant == "Fast" and wl.K >= 16 else 2
+    # Calls of more than one pass run the run kernels, unless they record.
+    run = args.calls == "run" and args.pi_scope == "element" and not args.pi_hist and wl.T > wl.K
     # The library streams (non-temporal accesses) when theta, h, theta* and the
     # snapshot/moment table outgrow the 256 MiB Infinity Cache.
     tiles = -(-(-(-wl.P // 64) * 64) // 8192)
@@ -328,8 +361,11 @@ def main() -> int:
     torch.cuda.synchronize()
 
     def step(k):
-        sl = slice(k * wl.T, (k + 1) * wl.T)
-        g.sim_run(worker[sl], tau[sl], wl.K)
+        end = (k + 1) * wl.T
+        each = wl.K if args.calls == "pass" else wl.T
+        for j in range(k * wl.T, end, each):
+            sl = slice(j, min(j + each, end))
+            g.sim_run(worker[sl], tau[sl], wl.K)
 
     for k in range(args.warmup):
         step(k)
@@ -355,35 +391,60 @@ def main() -> int:
     assert stats.commits == args.steps * wl.T
     g.close()
     copy_gbs = None if args.no_ceilings else copy_ceiling(G, torch, 2 << 30)
-    # The compute floor of a pass of K commits (not defined for the
-    # per-segment scope, whose commits are not fused).
-    floor_ms = (compute_floor(G, torch, wl, hp, cache, args.pi_hist) * wl.K
+    # The compute floor of a commit (not defined for the per-segment scope, whose
+    # commits are not fused).
+    floor_ms = (compute_floor(G, torch, wl, hp, cache, args.pi_hist, args.calls)
                 if args.pi_scope == "element" and not args.no_ceilings else None)
 
     elapsed = max(gpu_s, 1e-12)
     value = wl.P * stats.commits / elapsed
     passes = stats.passes
-    alg_per_pass = stats.alg_bytes / passes
-    avg_pass_s = elapsed / passes
-    achieved = alg_per_pass / avg_pass_s / 1e9
+    # What the timed launches read and write: a run's by its plan; a pass's, or a
+    # segment commit's, as the library counts them.
+    if run:
+        plans = [run_plan(wl, worker[k * wl.T:(k + 1) * wl.T], variant == "FastGlobal",
+                          args.rule == "adaptive") for k in range(args.warmup, args.warmup + args.steps)]
+        launches = sum(p["launches"] for p in plans)
+        nbytes = sum(p["bytes"] for p in plans)
+        short = sum(p["short"] for p in plans)
+        if args.cache == "auto":
+            streaming = streaming and 2 * sum(p["streaming"] for p in plans) > launches
+        kind = "short_run_kernel" if 2 * short > launches else "run_kernel"
+        kernel = "%s<%s%s>" % (kind, variant, ", streaming" if streaming and kind == "run_kernel" else "")
+    else:
+        launches, nbytes = passes, stats.alg_bytes
+        if args.pi_scope == "segment":
+            kind = "seg_step_kernel"
+            kernel = "seg_step_kernel + seg_blocks_kernel" + (", streaming" if streaming else "")
+        else:
+            kind = "pass_kernel"
+            # the default rule records through its recording pass, other variants
+            # through the diagnostic one (depth 2, default policy); a pass of one
+            # commit runs the kernel compiled for one commit
+            form = (", diagnostic, depth 2" if args.pi_hist and variant != "Fast"
+                    else "%s, depth %d%s" % (", recording" if args.pi_hist else "",
+                                             1 if wl.K == 1 and not args.pi_hist else depth,
+                                             ", streaming" if streaming else ""))
+            kernel = "pass_kernel<Generated, %s%s>" % (variant, form)
+    bytes_per_launch = nbytes / launches
+    avg_launch_s = elapsed / launches
+    achieved = bytes_per_launch / avg_launch_s / 1e9
     # The counter summaries were taken with the library's own cache rule.
     counted = (args.rule, args.pi, args.kappa) == ("gem", "clamp0", 1.0)
-    cnt = (measured_counters(wl.name, args.proxy, args.pi_scope)
+    cnt = (measured_counters(kind, wl.name, args.proxy)
            if counted and args.cache == "auto" and not args.pi_hist else None)
-    traffic = cnt.get("hbm_bytes_per_pass") if cnt else None
-    floor_share = floor_ms / (avg_pass_s * 1e3) if floor_ms else None
-    # The pass is reported against the ceiling it is nearer to: the compute
-    # floor of its arithmetic, or the library's copy rate on HBM.  A pass far
-    # from both (a launch-bound one over a tiny vector) keeps the HBM roofline.
+    traffic = cnt.get("bytes_per_launch") if cnt else None
+    floor_share = floor_ms * 1e-3 * stats.commits / elapsed if floor_ms else None
+    # The launches are reported against the ceiling they are nearer to: the compute
+    # floor of their arithmetic, or the library's copy rate on HBM.  Launches far
+    # from both (launch-bound ones over a tiny vector) keep the HBM roofline.
     if floor_share is not None and copy_gbs and floor_share > max(achieved / copy_gbs, 0.5):
-        valu = cnt.get("valu_instrs_per_pass") if cnt else None
-        ach = valu / avg_pass_s / 1e9 if valu else None
+        valu = cnt.get("valu_instrs_per_launch") if cnt else None
+        ach = valu / avg_launch_s / 1e9 if valu else None
         roof = {"bound": "alu", "achieved": ach, "peak": VALU_PEAK_GINST,
                 "unit": "G wave64 VALU instructions/s",
                 "frac": ach / VALU_PEAK_GINST if ach else None, "traffic": traffic,
                 "valu_instrs_per_launch": valu,
-                "unpacked_issue_peak": VALU_ISSUE_GINST,
-                "frac_of_unpacked_issue": ach / VALU_ISSUE_GINST if ach else None,
                 "hbm_GBps": achieved, "hbm_frac": achieved / HBM_PEAK_GBS}
     else:
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -412,32 +473,21 @@ def main() -> int:
             "passes_per_step": passes / args.steps,
             "rule": args.rule, "pi": args.pi, "proxy": args.proxy, "kappa": args.kappa,
             "pi_scope": args.pi_scope, "cache": args.cache, "pi_hist": args.pi_hist,
+            "calls": args.calls,
             "parallelism": "single-gpu",
         },
         "roofline": {
             **roof,
-            "alg_bytes_per_launch": alg_per_pass,
-            # A run's launches take many passes' commits and keep rows on the chip:
-            # they move fewer bytes than the passes of K commits counted here, and
-            # the algorithmic rate can exceed the memory's.
-            "alg_bytes_counted": "passes of at most K commits",
-            "avg_launch_ms": avg_pass_s * 1e3,
-            "kernel": (("seg_step_kernel + seg_blocks_kernel" + (", streaming" if streaming else ""))
-                       if args.pi_scope == "segment"
-                       # the default rule records through its recording pass; the
-                       # other variants through the diagnostic one (depth 2, default policy)
-                       else "pass_kernel<Generated, Fast, recording, depth %d%s>"
-                       % (depth, ", streaming" if streaming else "")
-                       if args.pi_hist and variant == "Fast"
-                       else "pass_kernel<Generated, %s, diagnostic, depth 2>" % variant
-                       if args.pi_hist
-                       # a pass of one commit runs the kernel compiled for one commit
-                       else "pass_kernel<Generated, %s, depth %d%s>"
-                       % (variant, 1 if wl.K == 1 else depth,
-                          ", streaming" if streaming else "")),
+            "alg_bytes_per_launch": bytes_per_launch,
+            "avg_launch_ms": avg_launch_s * 1e3,
+            "launches_per_step": launches / args.steps,
+            "kernel": kernel,
+            # what passes of at most K commits would move one by one, over the same time
+            # (a run keeps rows on the chip between passes, so this is no memory rate)
+            "pass_by_pass_GBps": stats.alg_bytes / elapsed / 1e9,
             "copy_ceiling_GBps": copy_gbs,
             "frac_of_copy": achieved / copy_gbs if copy_gbs else None,
-            "compute_floor_ms": floor_ms,
+            "compute_floor_ms": floor_share * avg_launch_s * 1e3 if floor_ms else None,
             "frac_of_compute_floor": floor_share,
         },
         "wall_s": wall,

@@ -313,20 +313,10 @@ int run_passes(gem_handle* g, const std::vector<Pass>& passes, Source src,
     return GEM_OK;
 }
 
-// Whether run_kernel's row accesses are non-temporal.  Rows stream when few of
-// them are found in the Infinity Cache again: beyond 250 workers (12.5M
-// parameters, 988 commits, 300 workers: 26.5 ms, default policy 27.2; 200: 24.5,
-// 23.6), or when a worker commits fewer than 1.4 times in the launch (25M
-// parameters, 100 workers, 48 commits: 2.59 ms, 2.82; 96 commits: 4.91, 4.56).
-bool stream_run(const gem_handle* g, int k, int64_t distinct)
-{
-    if (g->cache_policy != GEM_CACHE_AUTO) return g->cache_policy == GEM_CACHE_STREAM;
-    return stream_rows(g) && (distinct > 250 || 10 * k < 14 * distinct);
-}
-
 // Queue a run of T commits on generated updates as launches of up to
 // kRunCommits commits each; advance the clock and pull bookkeeping.  The work
-// counters count the passes of at most K commits that run_passes would launch.
+// counters count the passes of K commits (the last may be shorter) that run_passes
+// would launch: its planner cuts no pass at the ring depths in use (2 and 4).
 int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
 {
     gemk::RunArgs a;
@@ -369,8 +359,10 @@ int run_runs(gem_handle* g, const int32_t* worker, int64_t T, int32_t K)
             pull[w[j]] = next_pull(g, g->t + j);
         }
         const bool bf16 = g->sp.update_dtype == GEM_BF16;
+        const bool stream = stream_rows(g) && (g->cache_policy != GEM_CACHE_AUTO ||
+                                               gemk::stream_run(p.distinct, k));
         if (p.is_short) GEM_HIP(gemk::launch_short_run(a, variant, bf16, g->stream));
-        else GEM_HIP(gemk::launch_run(a, variant, bf16, stream_run(g, k, p.distinct),
+        else GEM_HIP(gemk::launch_run(a, variant, bf16, stream,
                                       static_cast<uint32_t>(p.slots * to.slot_bytes), g->stream));
         for (int j = 0; j < k; ++j) {
             g->pc[w[j]] = next_pull(g, g->t + j);

@@ -306,6 +306,14 @@ inline bool short_run(const RunTarget& to, int64_t distinct, int k)
     return per_cu <= (most < 8 ? most : 8);
 }
 
+// Whether run_kernel's accesses are non-temporal under GEM_CACHE_AUTO, where the
+// state outgrows the Infinity Cache: when few rows are found there again, that is
+// beyond 250 workers (12.5M parameters, 988 commits, 300 workers: 26.5 ms, default
+// policy 27.2; 200: 24.5, 23.6), or when a worker commits fewer than 1.4 times in
+// the launch (25M parameters, 100 workers, 48 commits: 2.59 ms, 2.82; 96 commits:
+// 4.91, 4.56).
+inline bool stream_run(int64_t distinct, int k) { return distinct > 250 || 10 * k < 14 * distinct; }
+
 // Plans a launch of k commits: the kernel, its slots, its schedule words.
 // run_kernel: 160 KiB of LDS per compute unit hold 20 slots (40 with the shared
 // moment's half slots), shared by the blocks resident there; measured at 12.5M

@@ -1,5 +1,6 @@
-// gem_selftest.hip -- device self-tests of the library's numerics (built as
-// libgem_selftest.so; not part of the commit path).
+// gem_selftest.hip -- device self-tests of the library's numerics, and the launches
+// that a run is planned as (built as libgem_selftest.so; not part of the commit
+// path).
 //
 // The commit kernels use range-specialised forms of correctly rounded
 // division and square root (gem_device.hpp).  These kernels compare them, on
@@ -24,8 +25,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/gem.h"
 #include "gem_device.hpp"
+#include "gem_plan.hpp"
 
 namespace {
 
@@ -332,6 +336,45 @@ int gem_selftest_div_grid(const float* nums, int32_t nnum, int32_t e_den, uint64
         }, mismatches);
     (void)hipFree(d_nums);
     return rc;
+}
+
+// The launches that gem_sim_run takes T commits in (T > K, eps >= 2^-60, no
+// diagnostics or recording), for the benchmark's labels and byte counts: out[0]
+// launches, out[1] of them of short_run_kernel, out[2] of run_kernel with
+// non-temporal accesses where the state outgrows the Infinity Cache, and out[3] the
+// row pieces (a worker's snapshot and moment; with `shared` its snapshot) read from
+// memory plus those written to it, in rows.  shared: the default rule with the
+// shared moment.  cus and lds (bytes a compute unit): 0 for the current device's.
+// Host only.
+int gem_selftest_run_plan(int64_t P, int32_t n, int32_t shared, int32_t adaptive,
+                          const int32_t* worker, int64_t T, int32_t cus, int32_t lds, int64_t* out)
+{
+    if (P < 1 || n < 1 || T < 0 || (T > 0 && !worker) || !out) return GEM_EINVAL;
+    for (int64_t j = 0; j < T; ++j)
+        if (worker[j] < 0 || worker[j] >= n) return GEM_EWORKER;
+    int device = 0;
+    if ((cus < 1 || lds < 1) &&
+        (hipGetDevice(&device) != hipSuccess ||
+         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+         hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device) !=
+             hipSuccess))
+        return GEM_EHIP;
+    const gemk::RunTarget to{(P + 63) / 64 * 64, cus, lds,
+                             shared ? gemk::kRunSlotBytes / 2 : gemk::kRunSlotBytes, adaptive != 0};
+    const int64_t most = gemk::run_commits(to), launches = (T + most - 1) / most;
+    std::vector<int32_t> last(static_cast<size_t>(n), -1);
+    std::vector<uint32_t> words(gemk::kRunWords);
+    out[0] = launches;
+    out[1] = out[2] = out[3] = 0;
+    for (int64_t l = 0, j0 = 0; l < launches; ++l) {
+        const int k = static_cast<int>((T - j0) / (launches - l));
+        const gemk::RunLaunch p = gemk::plan_launch(to, worker + j0, k, words.data(), last.data());
+        out[1] += p.is_short;
+        out[2] += !p.is_short && gemk::stream_run(p.distinct, k);
+        out[3] += p.moved;
+        j0 += k;
+    }
+    return GEM_OK;
 }
 
 }  // extern "C"

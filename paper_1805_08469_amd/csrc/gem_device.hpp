@@ -127,26 +127,27 @@ __device__ __forceinline__ float div_rn_core(float a, float b)
 // the compiler has the intrinsic but no builtin for it).
 __device__ float mul_legacy(float a, float b) __asm("llvm.amdgcn.fmul.legacy");
 
-// sqrt(x), correctly rounded, for the Box-Muller radicands x = -2 ln(k 2^-24),
-// k in [1, 2^24] (zero or in [1.1e-7, 33.3]).  One Newton step from the hardware
-// reciprocal root y: g = x y, then g + (x - g^2) (y / 2).  The step is the
-// correctly rounded root for every one of the 2^24 radicands (the self-test
-// library checks all of them on the device).  Five instructions and the root;
-// stepping v_sqrt's result to the neighbour with the right residual sign takes
-// eight.  y / 2 is an integer step of the exponent.
+// -sqrt(-x), the root correctly rounded, for the negated Box-Muller radicands
+// x = 2 ln(k 2^-24), k in [1, 2^24] (+0 or in [-33.3, -1.1e-7]).  One Newton step
+// from the hardware reciprocal root y of -x: n = x y, the negated root, then
+// n + (n^2 + x) (y / 2).  The step is the correctly rounded root for every one of
+// the 2^24 radicands (the self-test library checks all of them on the device).
+// Five instructions and the root; stepping v_sqrt's result to the neighbour with
+// the right residual sign takes eight.  y / 2 is an integer step of the exponent.
 //
-// The radicand of k = 2^24 is defined as -2 ln 1 = -0, whose root is -0; here it
-// arrives as +0 (radicand_of_k24).  Its y is inf and the legacy product, whose
-// zero times anything is +0, gives +0.  The step is therefore taken with both
-// signs turned, n = -g and -(x - g^2) = n^2 - x, which changes no bit of any
-// other root and ends here in (-0) 2^127 + (-0) = -0.
-__device__ __forceinline__ float radicand_root(float x)
+// The signs are turned for u = 1, whose radius is sqrt(-2 ln 1) = sqrt(-0) = -0.
+// There x is +0 and y is -inf; the legacy product, whose zero times anything is
+// +0, makes n = +0, and the step ends in (+0) (-2^127) + (+0) = +0: the radius
+// negated, with its sign.  (With r = x y from a positive x it would be +0 as well.)
+// They also spare the two multiply-adds their source modifiers, which take the
+// longer encoding.
+__device__ __forceinline__ float neg_radius(float x)
 {
-    const float y = __builtin_amdgcn_rsqf(x);
-    const float n = mul_legacy(x, -y);
+    const float y = __builtin_amdgcn_rsqf(-x);
+    const float n = mul_legacy(x, y);
     const float half_y = __uint_as_float(__float_as_uint(y) - 0x00800000u);
-    const float e = __builtin_fmaf(n, n, -x);
-    return __builtin_fmaf(-e, half_y, -n);
+    const float e = __builtin_fmaf(n, n, x);
+    return __builtin_fmaf(e, half_y, n);
 }
 
 // num / den, correctly rounded for every input: the core steps when both
@@ -179,7 +180,7 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 }
 
 // ---------------------------------------------------------------------------
-// The Box-Muller radicand -2 ln u of u = k * 2^-24, k in [1, 2^24].
+// 2 ln u of u = k * 2^-24, k in [1, 2^24]: the Box-Muller radicand -2 ln u, negated.
 // u = 2^e f with f in (sqrt(1/2), sqrt(2)]; ln f = 2 atanh((f-1)/(f+1)) by its
 // series to the s^9 term (Abramowitz & Stegun 4.1.27); ln u = e ln2 + ln f
 // with ln 2 split into a 15-bit head and a binary32 tail so that e * head is
@@ -188,12 +189,11 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 // The defined steps are p = ((s^2/9 + 1/7) s^2 + 1/5) s^2 + 1/3, p s^2, then
 // ln f = fma(2s, p s^2, 2s), ln u = fma(e, head, fma(e, tail, ln f)) and the
 // radicand -2 ln u.  Here every value carries the power-of-two factor that
-// makes the doublings and the final -2 disappear: s' = -4 s (the quotient of
-// -4 (f - 1), exact), s'^2 = 16 s^2 against coefficients divided by 16 per
-// degree, and the tail and head times -2.  Scaling by a power of two commutes
-// with rounding (nothing here is subnormal or overflows), so the bits are
-// those of the defined steps, in 2 instructions fewer; but for k = 2^24, whose
-// defined radicand is -0 and which is +0 here (radicand_root restores the sign).
+// makes the doublings disappear: s' = 4 s (the quotient of 4 (f - 1), exact),
+// s'^2 = 16 s^2 against coefficients divided by 16 per degree, and the tail and
+// head times 2.  Scaling by a power of two commutes with rounding (nothing here
+// is subnormal or overflows), so the bits are those of the defined steps, in 2
+// instructions fewer.
 //
 // The reduction works on the integer: k as binary32 (exact) has u's
 // significand and an exponent 24 larger; subtracting the bits of 2^24 * the
@@ -202,39 +202,39 @@ __device__ __forceinline__ float ln_quotient(float a, float b)
 // and k's bits less them are 2^24 f: the quotient of 2^24 (f - 1) and
 // 2^24 (f + 1) is the same.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float radicand_of_k24(uint32_t k)
+__device__ __forceinline__ float neg_radicand_of_k24(uint32_t k)
 {
     constexpr uint32_t kLeast = 0x3F3504F4u;   // least binary32 above sqrt(1/2)
     const uint32_t bits = __float_as_uint(static_cast<float>(k));
     const uint32_t eb = (bits - (kLeast + (24u << 23))) & 0xFF800000u;
     const float ef = static_cast<float>(static_cast<int32_t>(eb));          // 2^23 e
     const float f = __uint_as_float(bits - eb);                             // 2^24 f
-    const float s = ln_quotient(__builtin_fmaf(f, -4.0f, 0x1p26f), f + 0x1p24f);   // -4 (f-1)/(f+1)
+    const float s = ln_quotient(__builtin_fmaf(f, 4.0f, -0x1p26f), f + 0x1p24f);   // 4 (f-1)/(f+1)
     const float z = s * s;
     float p = (1.0f / 9.0f) * 0x1p-16f;
     p = __builtin_fmaf(p, z, (1.0f / 7.0f) * 0x1p-12f);
     p = __builtin_fmaf(p, z, (1.0f / 5.0f) * 0x1p-8f);
     p = __builtin_fmaf(p, z, (1.0f / 3.0f) * 0x1p-4f);
     p = p * z;
-    const float ln_f = __builtin_fmaf(s, p, s);   // -2 ln f
+    const float ln_f = __builtin_fmaf(s, p, s);   // 2 ln f
     const float ln2_tail = 0x1.7f7d1cp-20f;       // RN(ln 2 - ln2_head)
     const float ln2_head = 0x1.62e4p-1f;
-    const float r = __builtin_fmaf(ef, -2.0f * ln2_tail * 0x1p-23f, ln_f);
-    return __builtin_fmaf(ef, -2.0f * ln2_head * 0x1p-23f, r);
+    const float r = __builtin_fmaf(ef, 2.0f * ln2_tail * 0x1p-23f, ln_f);
+    return __builtin_fmaf(ef, 2.0f * ln2_head * 0x1p-23f, r);
 }
 
-// r cos(phi) and r sin(phi) for phi = 2 pi (xb >> 8) / 2^24.  With k = xb >> 8,
-// the angle is reduced to the nearest quarter turn on the integer, exactly;
-// the rest, |x| <= pi/4, goes through the Taylor series of sin (to x^9) and
-// cos (to x^10).  k minus its nearest multiple of 2^22 is k's low 22 bits
-// read as a signed number.
+// r cos(phi) and r sin(phi) for phi = 2 pi (xb >> 8) / 2^24, from neg_r = -r.
+// With k = xb >> 8, the angle is reduced to the nearest quarter turn on the
+// integer, exactly; the rest, |x| <= pi/4, goes through the Taylor series of sin
+// (to x^9) and cos (to x^10).  k minus its nearest multiple of 2^22 is k's low 22
+// bits read as a signed number.
 //
 // Quadrant q (bits 30 and 31 of xb + 2^29): (sin, cos) = (sx, cx), (cx, -sx),
 // (-sx, -cx), (-cx, sx): an odd quadrant takes (cx, -sx), and quadrants 2 and
 // 3 negate both, which here goes into r's sign before the two products (a
 // product's bits but for its sign do not depend on its factors' signs).  r may
 // be of either sign, zeros included: the radius of u1 = 1 is -0.
-__device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, float& zs)
+__device__ __forceinline__ void turn_times(float neg_r, uint32_t xb, float& zc, float& zs)
 {
     const int rem = static_cast<int>(xb << 2) >> 10;
     const float step = 6.28318530717958647692f * 0x1p-24f;   // RN(2 pi) 2^-24
@@ -258,9 +258,9 @@ __device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, floa
     // bit 30 of y = xb + 2^29: |y| as a binary32 is at least 2 (or a NaN) with it
     const uint32_t y = xb + 0x20000000u;
     const bool odd = !(__builtin_fabsf(__uint_as_float(y)) < 2.0f);
-    // r ^ (y & sign bit): one V_BITOP3_B32 (a ^ (b & c), table 0x78)
+    // neg_r ^ (~y & sign bit): one V_BITOP3_B32 (a ^ (~b & c), table 0xD2)
     const float rs = __uint_as_float(__builtin_amdgcn_bitop3_b32(
-        __float_as_uint(r), y, 0x80000000u, 0x78));
+        __float_as_uint(neg_r), y, 0x80000000u, 0xD2));
     zs = rs * (odd ? cx : sx);
     zc = rs * (odd ? -sx : cx);
 }
@@ -269,7 +269,7 @@ __device__ __forceinline__ void turn_times(float r, uint32_t xb, float& zc, floa
 // the angle index xb >> 8, the pair r cos(phi), r sin(phi), r = sqrt(-2 ln u1).
 __device__ __forceinline__ void box_muller(uint32_t xa, uint32_t xb, float& zc, float& zs)
 {
-    turn_times(radicand_root(radicand_of_k24((xa >> 8) + 1u)), xb, zc, zs);
+    turn_times(neg_radius(neg_radicand_of_k24((xa >> 8) + 1u)), xb, zc, zs);
 }
 
 // Four standard normals for elements 4q..4q+3 at clock t.  UNIFORM: t is the

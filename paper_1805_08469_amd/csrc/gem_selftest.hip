@@ -111,10 +111,9 @@ __global__ __launch_bounds__(kThreads) void radius_kernel(unsigned long long* ba
 {
     const uint32_t k = blockIdx.x * kThreads + threadIdx.x + 1u;   // 1 .. 2^24
     const float want = -2.0f * defined_ln(static_cast<float>(k) * 0x1p-24f);
-    const float x = gemk::radicand_of_k24(k);
-    // the radicand of u = 1 is -0 as defined and arrives as +0; the root is -0
-    if (!same_bits(x, k == (1u << 24) ? 0.0f : want)) atomicAdd(bad, 1ull);
-    if (!same_bits(gemk::radicand_root(x), __builtin_sqrtf(want))) atomicAdd(bad, 1ull);
+    const float x = gemk::neg_radicand_of_k24(k);
+    if (!same_bits(-x, want)) atomicAdd(bad, 1ull);
+    if (!same_bits(-gemk::neg_radius(x), __builtin_sqrtf(want))) atomicAdd(bad, 1ull);
 }
 
 __global__ __launch_bounds__(kThreads) void turn_kernel(float r, unsigned long long* bad)
@@ -123,7 +122,7 @@ __global__ __launch_bounds__(kThreads) void turn_kernel(float r, unsigned long l
     float sn, cs, zc, zs;
     defined_sincos(k, sn, cs);
     // (the word's low 8 bits do not enter)
-    gemk::turn_times(r, (k << 8) | ((k * 37u) & 255u), zc, zs);
+    gemk::turn_times(-r, (k << 8) | ((k * 37u) & 255u), zc, zs);
     if (!same_bits(zc, r * cs)) atomicAdd(bad, 1ull);
     if (!same_bits(zs, r * sn)) atomicAdd(bad, 1ull);
 }

@@ -230,7 +230,10 @@ int gem_schedule_make(int32_t n, int64_t T, const gem_schedule_law* law, uint64_
  * unit of the work counters.  A call of one pass (T <= K), and passes with
  * diagnostics or histograms enabled, are launched pass by pass (under
  * GEM_PI_SEGMENT K is checked but each commit is applied on its own).  Needs
- * gem_set_quadratic.  Errors: ESTATE, EINVAL, EWORKER, ESTALE. */
+ * gem_set_quadratic.  A launch is of at most 2^36 element-commits (32 commits, if
+ * P is too large for more): it may hold the GPU from other streams for a tenth of
+ * a second or so (25M parameters: 34 ms), where a pass of 32 commits took 2 ms.
+ * Errors: ESTATE, EINVAL, EWORKER, ESTALE. */
 int gem_sim_run(gem_t* g, const int32_t* worker, const int32_t* tau, int64_t T, int32_t K);
 
 /* Copy theta (P floats) to out (host, or device if out_is_device). */
@@ -379,9 +382,10 @@ int gem_load(gem_t* g, const char* path);
  * 256 MiB Infinity Cache stays there between passes (streaming it is 14-24%
  * slower).  GEM_CACHE_AUTO (the default) streams when theta, h, theta* and
  * the snapshot and moment table together exceed 256 MiB; a launch of many
- * passes then streams only its rows, and only when its workers are too many
- * (over 250) or its commits too few (under 1.4 a worker) for the cache to
- * hold a row until its worker's next commit.  Results are the
+ * passes then streams its rows, h and theta* (not theta), and only when its
+ * workers are too many (over 250) or its commits too few (under 1.4 a worker)
+ * for the cache to hold a row until its worker's next commit; the kernel for
+ * short vectors, which touches memory once a launch, has one policy.  Results are the
  * same bits under every policy.  The diagnostic passes keep the default
  * policy; so do the per-segment scope's loads of h and theta*, which every
  * commit reads: with the other streams non-temporal the Infinity Cache keeps

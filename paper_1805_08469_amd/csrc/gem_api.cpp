@@ -223,7 +223,6 @@ void base_args(const gem_handle* g, PassArgs& a)
     a.mode = mode_bits(g->hp);
 }
 
-// Queue the planned passes; advance the clock and pull bookkeeping.
 // The ring depth of a run's passes: the deep ring for the default rule with
 // per-worker moments on generated updates in passes of at least kDeepMinK
 // commits, without diagnostics or recording.
@@ -243,6 +242,7 @@ bool stream_rows(const gem_handle* g)
     return bytes > gemk::kInfinityCacheBytes;
 }
 
+// Queue the planned passes; advance the clock and pull bookkeeping.
 int run_passes(gem_handle* g, const std::vector<Pass>& passes, Source src,
                const void* const* upd, bool bf16_out, int depth)
 {

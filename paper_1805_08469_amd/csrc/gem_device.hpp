@@ -132,7 +132,7 @@ __device__ float mul_legacy(float a, float b) __asm("llvm.amdgcn.fmul.legacy");
 // from the hardware reciprocal root y of -x: n = x y, the negated root, then
 // n + (n^2 + x) (y / 2).  The step is the correctly rounded root for every one of
 // the 2^24 radicands (the self-test library checks all of them on the device).
-// Five instructions and the root; stepping v_sqrt's result to the neighbour with
+// Four instructions and the root; stepping v_sqrt's result to the neighbour with
 // the right residual sign takes eight.  y / 2 is an integer step of the exponent.
 //
 // The signs are turned for u = 1, whose radius is sqrt(-2 ln 1) = sqrt(-0) = -0.

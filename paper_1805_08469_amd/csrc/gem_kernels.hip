@@ -1,18 +1,23 @@
 // gem_kernels.hip -- HIP kernels of the GEM commit pipeline for gfx950.
 //
-// The hot kernel is one fused pass: every thread owns four consecutive
-// parameters (one 16-byte chunk of every row) and applies the pass's K
-// commits to them in clock order.  theta, h and theta* are read once per
-// pass and theta written once; a worker's snapshot and moment chunks are
-// read (prefetched two commits ahead) at its first commit in the pass and
-// written at its last, held in registers in between.  Rows are read and
-// written as 128-bit accesses, consecutive lanes on consecutive chunks, so
-// every wavefront moves 1 KiB contiguous per row.  There is no contraction:
-// the work is streaming elementwise arithmetic (Philox, Box-Muller, the GEM
-// step), bounded by HBM bandwidth and VALU issue, so no MFMA is involved.
+// The work is elementwise and streaming (Philox, Box-Muller, the GEM step): there
+// is no contraction, so no MFMA is involved, and the bounds are VALU issue and the
+// snapshot and moment rows between the caches and the chip.
 //
-// Also here: the per-segment variant of the scale factor (a streaming step
-// kernel plus two small tree reductions per commit), the stand-alone update
+// Simulated runs of more than one pass go to run_kernel, or over a short vector to
+// short_run_kernel: a block takes its elements through up to 993 commits, with rows
+// of workers that commit again soon in LDS.  Calls of one pass, caller updates,
+// diagnostics and recordings go to pass_kernel: every thread owns four consecutive
+// parameters (one 16-byte chunk of every row) and applies the pass's K commits to
+// them in clock order.  theta, h and theta* are read once per pass and theta written
+// once; a worker's snapshot and moment chunks are read (prefetched two or four
+// commits ahead) at its first commit in the pass and written at its last, held in
+// registers in between.  In both, rows are read and written as 128-bit accesses,
+// consecutive lanes on consecutive chunks, so every wavefront moves 1 KiB contiguous
+// per row (the short-vector kernel: 4-byte ones, once a launch).
+//
+// Also here: the per-segment variant of the scale factor (per commit a streaming
+// step kernel and one launch that sums and forms the factors), the stand-alone update
 // generator, and small gather, fill, loss and copy kernels.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -882,11 +887,15 @@ __device__ __forceinline__ void put_row_at(float* base, bool mem, uint32_t byte_
 //   - theta, h and theta* are read once per run instead of once per pass;
 //   - the rows a block moves again lie in the Infinity Cache's share of the
 //     few hundred blocks in flight, if the workers are not too many.
-// What is left is 197 VALU instructions per wave and commit (203 with bf16
-// updates), one per SIMD every four cycles when all rows stay in LDS, and the rows'
-// traffic between L2 and the fabric at 6.0-6.6 TB/s, the rate a copy reaches.
+// What is left is 201 VALU instructions per wave and commit by the counters (209
+// with bf16 updates), and the rows' traffic between L2 and the fabric, 10.0 bytes an
+// element-commit at 25M parameters and 100 workers, at 6.2-6.4 TB/s, the rate a copy
+// reaches.  The step's 192 instructions take 580 cycles of a SIMD: 110 issue every
+// two cycles, 74 every four (64-bit multiply-adds, conversions, comparisons, minima
+// and maxima, and any that reads a scalar register), 8 every eight.  The counters
+// show up to 1.21 of them per SIMD in four cycles.
 // Measured at 25M parameters and 100 workers, 1000 commits: 56.4 ms in passes of
-// 32, 40.8 ms here; with the shared moment 40.7 and 31.5 (VALU issue at 0.99).
+// 32, 40.8 ms here; with the shared moment 40.7 and 31.5 (bound by VALU issue).
 //
 // Two elements a thread, a lane pair sharing a Philox block, would give each
 // element twice the slots: 221 instructions, and within 2% at every size.
@@ -1002,8 +1011,9 @@ __global__ __launch_bounds__(kBlock, 4) void run_kernel(const RunArgs a)
 // their 192 lanes: 24 commits x 16 Philox blocks).  The consumer's chain is 25
 // vector instructions and no memory but LDS, read one commit ahead; a worker that
 // commits twice in a row hands its rows over in registers.  The consumer's place
-// among the block's waves, which the hardware spreads over the SIMDs, rotates
-// with the blocks of a compute unit.
+// among the block's waves, which the hardware spreads over the SIMDs, changes every
+// 256 blocks, the compute units of this chip: its consumers then share the SIMDs.
+// (A tuning constant: another number of units would only spread them less evenly.)
 //
 // a.sched: the commits' slots, two 16-bit numbers a word; then each slot's worker;
 // the staleness values from kRunTauAt on; the number of slots in the last word.

@@ -329,7 +329,9 @@ inline bool stream_run(int64_t distinct, int k) { return distinct > 250 || 10 * 
 //     6.93, 3 blocks 7.39; 990 commits, 0.71: 40.3, 41.2; 124M, 64 workers, 160
 //     commits of a Pareto schedule, 0.86: 35.0, 38.1; 150 workers: 21.7, 25.2; 300:
 //     27.2, 30.0).  The shared moment moves half as much and keeps 3 blocks
-//     (300 workers: 17.2, 2 blocks 18.1).
+//     (300 workers: 17.2, 2 blocks 18.1).  At the line itself the two are within 3%:
+//     schedules whose share lies about it (25M, 100 workers: 0.67 to 0.71) may go
+//     either way from launch to launch, at no greater difference than that.
 // last: scratch of one int per worker (-1 on entry and on return).
 inline RunLaunch plan_launch(const RunTarget& to, const int32_t* worker, int k, uint32_t* words,
                              int32_t* last)
